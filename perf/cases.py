@@ -150,6 +150,39 @@ def run(s):
     return {"y": y.detach(), "dx": dx, "dw": dw, "db": db}
 
 
+def exact(case, seed):
+    """The passes in 64 bits with plain torch: one product of matrices per tap."""
+    s = prepare(case, seed)
+    w, d, P = s["w"] if "w" in s else s["net"].weight, s["d"], s["P"]
+    x, w = s["x"].detach().double(), w.detach().double()
+    W, S = x.shape[2], w.shape[2]
+    Q = W + 2 * P - (S - 1) * d
+    if s["N"] * max(s["C"] * (W + 2 * P), s["K"] * Q) > 3e8:
+        return None
+    xp = torch.nn.functional.pad(x, (P, P))
+    z = torch.zeros((s["N"], s["K"], Q), dtype=torch.float64, device="cuda")
+    for t in range(S):
+        z += torch.matmul(w[:, :, t].contiguous(), xp[:, :, t * d:t * d + Q].contiguous())
+    if s["use"] != "step":
+        bias = s["bias"] if "bias" in s else s["net"].bias
+        z = (z + bias.detach().double()[None, :, None]).clamp(min=0)
+    if s["use"] == "infer":
+        return z
+    g = s["dy"].double()
+    if s["use"] == "train":
+        g = g * (z > 0)
+    dxp = torch.zeros_like(xp)
+    dw = torch.empty_like(w)
+    gt = g.transpose(1, 2).contiguous()
+    for t in range(S):
+        dxp[:, :, t * d:t * d + Q] += torch.matmul(w[:, :, t].t().contiguous(), g)
+        dw[:, :, t] = torch.matmul(xp[:, :, t * d:t * d + Q].contiguous(), gt).sum(0).t()
+    r = {"y": z, "dx": dxp[:, :, P:P + W].contiguous(), "dw": dw}
+    if s["use"] == "train":
+        r["db"] = g.sum((0, 2))
+    return r
+
+
 def work(case):
     """Each input read once, each output written once; 2 N C K S Q operations per pass."""
     N, C, K, W, S, d, P = (case[k] for k in ("N", "C", "K", "W", "S", "d", "P"))
