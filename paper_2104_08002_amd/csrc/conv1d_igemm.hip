@@ -57,6 +57,7 @@ bool fp32_pairs_in_one_launch(const WgradProblem& p) {
 enum class CorrRoute {
     kNone,
     kRing, kStream, kStaged,   // bf16: one launch of a many-channel kernel
+    kF32Split,                 // fp32: one launch on the bf16 matrix instructions
     kF32Whole,                 // fp32: one launch, channel blocks reduced in the accumulators
     kF32PerChannelBlock,       // fp32: one launch per channel block, accumulating into the output
     kRows,                     // one launch per filter block (each reduces its channel blocks itself)
@@ -74,6 +75,7 @@ CorrRoute corr_route(const CorrProblem& p) {
     if (p.bf16 && igemm_bf16_corr_supported(p)) return CorrRoute::kStaged;
     if (p.R <= kBlock && p.M <= kBlock) return CorrRoute::kNone;  // one block: that is the small-channel family itself
     if (!smallc_corr_supported(corr_block(p, 0, 0))) return CorrRoute::kNone;  // the first block pair is the largest one
+    if (split_f32_corr_supported(p)) return CorrRoute::kF32Split;
     if (!p.bf16) {
         CorrProblem whole = p;
         whole.w_contig = 0;
@@ -108,6 +110,7 @@ hipError_t igemm_corr_launch(const CorrProblem& p, hipStream_t st) {
         case CorrRoute::kRing: return igemm_ring_bf16_corr_launch(p, st);
         case CorrRoute::kStream: return igemm_stream_bf16_corr_launch(p, st);
         case CorrRoute::kStaged: return igemm_bf16_corr_launch(p, st);
+        case CorrRoute::kF32Split: return split_f32_corr_launch(p, st);
         case CorrRoute::kF32Whole: {
             // every filter block in one launch: the kernel holds the weights of all channel blocks of a block
             CorrProblem whole = p;

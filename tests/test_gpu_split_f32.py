@@ -1,0 +1,56 @@
+"""FP32 layers on the bf16 matrix instructions (three bfloat16 parts per float), at the sizes where their tiles end.
+
+Bound: against the 64-bit oracle every output stays within 2e-6 of sum|products|.  The parts leave 2^-25 of a product
+out, partial sums of at most 128 terms are rounded 24 times at 2^-24 of their size and joined to a second sum every 128
+terms: 24 * 2^-24 = 1.4e-6 if every rounding fell the same way; measured maxima are a tenth of that.
+"""
+import pytest
+
+from paper_2104_08002_amd import inputs
+from parity_util import check_full, gpu_passes, to_device
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-6
+
+CASES = [
+    # N  C   K    W     S   d   P
+    (1, 17, 1,   16,   1,  1,  0),    # one tap, one tile far from full, a channel block of one channel
+    (2, 33, 17,  257,  2,  1,  1),    # one column and one filter past a tile, width not a multiple of 4
+    (1, 40, 49,  320,  3,  5,  5),    # four filter blocks, the last of one filter; width = one 320-column tile
+    (3, 64, 65,  511,  5,  16, 32),   # a second filter group of one filter
+    (1, 24, 40,  1285, 7,  3,  30),   # padding past the halo, width one past 5 x 257
+    (2, 16, 80,  384,  4,  64, 0),    # few channels, many filters; a window mostly of halo
+    (1, 130, 20, 768,  9,  2,  8),    # channels two past 4 x 32, three tiles of 256 exactly
+    (1, 64, 64,  1000, 52, 8,  204),  # most taps
+    (1, 20, 20,  3200, 52, 20, 510),  # a halo of 1020 columns
+]
+
+
+@pytest.fixture(scope="module")
+def binding():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2104_08002_amd import binding as b
+
+    b.load()
+    yield b
+    b.conv1d_set_variant(0)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_split_layers(binding, case):
+    import oracle
+
+    oracle.build()
+    N, C, K, W, S, d, P = case
+    wl = inputs.scaled(inputs.TINY, name="split_" + "_".join(map(str, case)), N=N, C=C, K=K, W=W, S=S, d=d, P=P,
+                       x_dist="normal", w_dist="normal_fan", dy_dist="normal", seed=inputs.BASE_SEED + 7000 + W + S)
+    binding.conv1d_set_variant(0)
+    for i in range(3):
+        assert "mfma" in binding.conv1d_kernel_name(i, *wl.geometry(), 0)
+    data = inputs.make_inputs(wl)
+    errs = check_full(oracle, wl, data, gpu_passes(wl, to_device(wl, data)))
+    print(case, errs, flush=True)
+    assert all(e <= TOL for e in errs.values()), errs
