@@ -182,7 +182,7 @@ hipError_t igemm_wgrad_launch(const WgradProblem& p, hipStream_t st) {
     if (prefer_shift_wgrad(p)) return shift_bf16_wgrad_launch(p, st);
     if (p.bf16 && toeplitz_bf16_wgrad_supported(p)) return toeplitz_bf16_wgrad_launch(p, st);
     if (p.bf16 && blocked_bf16_wgrad_supported(p)) return blocked_bf16_wgrad_launch(p, st);
-    if (fp32_pairs_in_one_launch(p)) return smallc_wgrad_f32_blocks_launch(p, st);
+    if (fp32_pairs_in_one_launch(p)) return split_f32_wgrad_supported(p) ? split_f32_wgrad_launch(p, st) : smallc_wgrad_f32_blocks_launch(p, st);
     for (int k0 = 0; k0 < p.K; k0 += kBlock) {
         for (int c0 = 0; c0 < p.C; c0 += kBlock) {
             const WgradProblem b = wgrad_block(p, k0, c0);

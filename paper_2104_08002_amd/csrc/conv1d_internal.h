@@ -146,6 +146,9 @@ hipError_t igemm_stream_bf16_corr_launch(const CorrProblem& p, hipStream_t st);
 // FP32 forward / backward-data on the bf16 matrix instructions: every float as the sum of three bfloat16 numbers
 bool split_f32_corr_supported(const CorrProblem& p);
 hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st);
+// FP32 backward-weight the same way; workspace and second stage of smallc_wgrad_f32_blocks_*
+bool split_f32_wgrad_supported(const WgradProblem& p);
+hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st);
 
 // channel-blocked MFMA family
 bool igemm_corr_supported(const CorrProblem& p);

@@ -41,5 +41,11 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The six products of a step start from zero, smallest first, and their sum is added to the running one in an ordinary
+// FP32 addition.  Chained through the running sums themselves the matrix instruction's additions lost more than the
+// FP32 instruction's did: error of a weight gradient of 3.4 million terms against 64 bits 2.9e-5 so, 8.2e-6 with
+// v_mfma_f32_16x16x4_f32.
+constexpr int kPartA[6] = {2, 0, 1, 1, 0, 0}, kPartB[6] = {0, 2, 1, 0, 1, 0};
+
 }  // namespace sp
 }  // namespace conv1d

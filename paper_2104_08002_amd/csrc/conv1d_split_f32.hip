@@ -3,10 +3,9 @@
 // v_mfma_f32_16x16x4_f32 does 1/16 of the operations per cycle that v_mfma_f32_16x16x32_bf16 does, and the FP32 passes
 // were bound by it.  Here each float is the sum of three bfloat16 numbers (conv1d_split_f32.h) and a product is the six
 // largest of their nine products, exact in the matrix unit and added in FP32: 6/16 of the FP32 matrix time.  The
-// products left out are 2^-25 of the whole with either sign, less than one FP32 rounding.  The accumulators of four
-// steps (128 terms) are added to a second set of registers and start again from zero: a sum of n terms is then rounded
-// n/128 times at full size where the FP32 instruction rounded it n/4 times, and the error against 64 bits fell on
-// every geometry measured (without the second set it rose for long reductions, C = 192, S = 15: 8.3e-7 against 2.9e-7).
+// products left out are 2^-25 of the whole with either sign, less than one FP32 rounding.  The sum of the six over
+// 32 terms is added to the running sums in FP32, so a sum of n terms is rounded n/32 times at full size where the FP32
+// instruction rounded it n/4 times: the error against 64 bits fell on every geometry measured.
 //
 // One workgroup: 16 FBW filters x 64 PB output columns of one sample, wave v the columns 16 PB v ..  A step is one
 // matrix instruction deep (32 = 4 lane groups x 8 channels): PL planes of 8 channels times 4/PL taps.  The input
@@ -21,7 +20,6 @@ namespace {
 using namespace sp;
 
 constexpr int kThreads = 256;
-constexpr int kFold = 4;  // steps between two additions to the second set of sums
 constexpr size_t kLdsHalf = 80 * 1024, kLdsAll = 160 * 1024;
 
 struct SpArgs {
@@ -57,19 +55,22 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
     const float* wrow = a.wt + min(em, a.M - 1) * a.w_sm + a.w_s0;
     const int eplane = g & (PL - 1), etap = g >> a.pl_sh;
     float wv[8];
+    int cleft = 0;
     auto request = [&](int stage, int step) {
         if (!has_entry) return;
         const int tap = step * TP + etap, c = 8 * (stage * PL + eplane);
         const float* p = wrow + static_cast<long>(min(tap, a.S - 1)) * a.w_ss;
-        const int cmax = (em < a.M && tap < a.S) ? a.R : 0;
+        cleft = (em < a.M && tap < a.S) ? a.R - c : 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float v = p[min(c + j, a.R - 1) * a.w_sr];
-            wv[j] = c + j < cmax ? v : 0.f;
-        }
+        for (int j = 0; j < 8; ++j) wv[j] = p[min(c + j, a.R - 1) * a.w_sr];
     };
+    // channels, taps and filters the layer does not have count as zero; put right here, so that nothing waits for the
+    // loads before the products of a step are done
     auto park = [&](int buf) {
         if (!has_entry) return;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (j >= cleft) wv[j] = 0.f;
         const Split8 s = split8(wv);
         u32x4* e = ws + (buf * FBW + (tid >> 6)) * 192 + lane;
         e[0] = s.h;
@@ -77,36 +78,44 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
         e[128] = s.l;
     };
 
-    f32x4 acc[PB][FBW], sum[PB][FBW];
+    f32x4 acc[PB][FBW];
 #pragma unroll
     for (int t = 0; t < PB; ++t)
 #pragma unroll
-        for (int f = 0; f < FBW; ++f) acc[t][f] = sum[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int until_fold = kFold;
+        for (int f = 0; f < FBW; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     request(0, 0);
     int buf = 0;
     const int rd0 = (g & (PL - 1)) * a.wlen + (g >> a.pl_sh) * a.d + wave * (16 * PB) + l16;
     for (int stage = 0; stage < a.nstages; ++stage) {
         const int col0 = q0 - a.P;
-        int plane = 0, pos = tid;
-        while (pos >= a.wlen) pos -= a.wlen, ++plane;
-        while (plane < PL) {
-            const int c = 8 * (stage * PL + plane), col = col0 + pos;
-            const bool inside = col >= 0 && col < a.Win;
-            const float* p = inb + clampi(col, 0, a.Win - 1);
-            float v[8];
+        // four slots per thread in flight
+        for (int i0 = tid; i0 < part; i0 += 4 * kThreads) {
+            float v[4][8];
+            int cl[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = p[static_cast<long>(min(c + j, a.R - 1)) * a.Win];
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + k * kThreads, part - 1);
+                const int plane = (i >= a.wlen) + (i >= 2 * a.wlen) + (i >= 3 * a.wlen);
+                const int c = 8 * (stage * PL + plane), col = col0 + i - plane * a.wlen;
+                const float* p = inb + clampi(col, 0, a.Win - 1);
+                cl[k] = (col >= 0 && col < a.Win) ? a.R - c : 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (inside && c + j < a.R) ? v[j] : 0.f;
-            const Split8 s = split8(v);
-            u32x4* x = xs + plane * a.wlen + pos;
-            x[0] = s.h;
-            x[part] = s.m;
-            x[2 * part] = s.l;
-            pos += kThreads;
-            while (pos >= a.wlen) pos -= a.wlen, ++plane;
+                for (int j = 0; j < 8; ++j) v[k][j] = p[static_cast<long>(min(c + j, a.R - 1)) * a.Win];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + k * kThreads;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j >= cl[k]) v[k][j] = 0.f;
+                const Split8 s = split8(v[k]);
+                if (i < part) {
+                    xs[i] = s.h;
+                    xs[part + i] = s.m;
+                    xs[2 * part + i] = s.l;
+                }
+            }
         }
         if (stage == 0) park(0);
         __syncthreads();
@@ -119,36 +128,40 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
             for (int f = 0; f < FBW; ++f)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) w[f][i] = ws[(buf * FBW + f) * 192 + i * 64 + lane];
-            constexpr int U = FBW >= 4 ? 1 : (FBW == 1 ? 4 : 2);  // column blocks in turn: no product waits for the one before
-#pragma unroll
-            for (int t0 = 0; t0 < PB; t0 += U) {
-                u32x4 x[U][3];
+            constexpr int U = FBW >= 3 ? 1 : 2;  // column blocks in turn: no product waits for the one before
+            // the reads of the next blocks in front of the products of these, and no earlier (registers)
+            u32x4 xr[2][U][3];
+            auto read = [&](int t0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (t0 + u < PB)
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) x[u][i] = xs[i * part + rd + 16 * (t0 + u)];
-                constexpr int px[6] = {2, 0, 1, 1, 0, 0}, pw[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
+                        for (int i = 0; i < 3; ++i) xr[(t0 / U) & 1][u][i] = xs[i * part + rd + 16 * (t0 + u)];
+            };
+            read(0);
+#pragma unroll
+            for (int t0 = 0; t0 < PB; t0 += U) {
+                if (t0 + U < PB) read(t0 + U);
+                __builtin_amdgcn_sched_barrier(0);
+                const auto& x = xr[(t0 / U) & 1];
+                f32x4 sum[U][FBW];
 #pragma unroll
                 for (int k = 0; k < 6; ++k)
 #pragma unroll
                     for (int u = 0; u < U; ++u)
                         if (t0 + u < PB)
 #pragma unroll
-                            for (int f = 0; f < FBW; ++f) acc[t0 + u][f] = mfma(x[u][px[k]], w[f][pw[k]], acc[t0 + u][f]);
+                            for (int f = 0; f < FBW; ++f)
+                                sum[u][f] = mfma(x[u][kPartA[k]], w[f][kPartB[k]], k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[u][f]);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (t0 + u < PB)
+#pragma unroll
+                        for (int f = 0; f < FBW; ++f) acc[t0 + u][f] += sum[u][f];
+                __builtin_amdgcn_sched_barrier(0);
             }
             buf ^= 1;
             if (more) park(buf);
-            if (--until_fold == 0) {
-                until_fold = kFold;
-#pragma unroll
-                for (int t = 0; t < PB; ++t)
-#pragma unroll
-                    for (int f = 0; f < FBW; ++f) {
-                        sum[t][f] += acc[t][f];
-                        acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    }
-            }
             __syncthreads();
         }
     }
@@ -164,7 +177,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
 #pragma unroll
         for (int t = 0; t < PB; ++t) {
             const int q = q0 + (wave * PB + t) * 16 + 4 * g;
-            const f32x4 v = epi_apply4(a.epi, sum[t][f] + acc[t][f], bias);
+            const f32x4 v = epi_apply4(a.epi, acc[t][f], bias);
             if (a.vec) {
                 if (q < a.Wout) *reinterpret_cast<f32x4*>(out + row + q) = v;
             } else {
@@ -191,8 +204,7 @@ Plan make_plan(const CorrProblem& p) {
     double best_cost = 0;
     for (int fbw = 1; fbw <= 4; ++fbw) {
         for (int pb = 4; pb <= 8; ++pb) {
-            // two sets of 4 FBW PB sums, 12 FBW weight and 12 to 48 input registers within 256
-            if (pb == 7 || (fbw == 4 && pb > 5) || (fbw == 3 && pb > 6)) continue;
+            if (pb == 7 || fbw * pb > 20) continue;  // sums, weights and inputs within 256 registers
             const int qtiles = cdiv(p.Wout, 64 * pb), fgroups = cdiv(mb, fbw);
             const long grid = static_cast<long>(p.N) * qtiles * fgroups;
             if (grid > 0x7fffffffL / kThreads) continue;

@@ -83,6 +83,9 @@ inline unsigned hostmodel_alignbit(unsigned hi, unsigned lo, unsigned sh) {
 }
 #define __builtin_amdgcn_alignbit(a, b, s) hostmodel_alignbit(a, b, s)
 
+// transposing LDS read: the lane's own 8 bytes (in the GPU's version other lanes of the 16 supply the values)
+#define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) (*(p))
+
 // raw buffer loads: the descriptor is the base address, the load an ordinary (guard-checked) read
 struct hostmodel_rsrc {
     const char* base;
