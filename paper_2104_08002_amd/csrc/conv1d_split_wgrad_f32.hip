@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a)
         const int f = min(tid + k * kThreads, ndy - 1) >> (a.qc_sh + 1);
         dyrow[k] = 4u * static_cast<unsigned>(min(k0 + 16 * f + (tid & 15), a.K - 1) * a.Q);
     }
-    auto request = [&](int u, Set& set) {
+    auto request = [&](int u, Set& set) __attribute__((always_inline)) {
         auto& dv = set.dv;
         auto& xv = set.xv;
         const int n = u / a.upr, q0 = (u - n * a.upr) << a.qc_sh;
@@ -110,10 +110,13 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a)
             for (int e = 0; e < 8; ++e) xv[k][e] = *reinterpret_cast<const float*>(xb + (xrow[e] + col));
         }
     };
-    auto park = [&](int u, u32x4* b, Set& set) {
+    auto park = [&](int u, u32x4* b, Set& set) __attribute__((always_inline)) {
         auto& dv = set.dv;
         auto& xv = set.xv;
         const int n = u / a.upr, q0 = (u - n * a.upr) << a.qc_sh;
+        // The matrix instruction cuts sums off towards minus infinity, which adds up over millions of terms: every other
+        // unit is multiplied with -dy and subtracted, so that the offsets cancel.
+        const unsigned sign = ((u - u_begin) & 1) ? 0x80000000u : 0u;
 #pragma unroll
         for (int k = 0; k < kDyTasks; ++k) {
             const int i = tid + k * kThreads;
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a)
                 const int left = k0 + 16 * f + (i & 15) < a.K ? a.Q - (q0 + 32 * (j >> 2) + 4 * (j & 3)) : 0;
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    if (16 * (e >> 2) + (e & 3) >= left) dv[k][e] = 0.f;
+                    dv[k][e] = 16 * (e >> 2) + (e & 3) >= left ? 0.f : __uint_as_float(__float_as_uint(dv[k][e]) ^ sign);
                 const Split8 s = split8(dv[k]);
                 b[i] = s.h;
                 b[ndy + i] = s.m;
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a)
         for (int f = 0; f < FBW; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // unit u, the PAR-th of the strip modulo 2
-    auto unit = [&](int u, auto par) {
+    auto unit = [&](int u, auto par) __attribute__((always_inline)) {
         constexpr int PAR = decltype(par)::value;
         const u32x4* cur = lds + PAR * stage;
         auto refill = [&] {
@@ -210,7 +213,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a)
                 for (int v = 0; v < U; ++v)
                     if (t + v < NTW)
 #pragma unroll
-                        for (int f = 0; f < FBW; ++f) acc[t + v][f] += part[v][f];
+                        for (int f = 0; f < FBW; ++f) acc[t + v][f] = PAR ? acc[t + v][f] - part[v][f] : acc[t + v][f] + part[v][f];
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
