@@ -23,6 +23,7 @@ CASES = [
     (2, 16, 80,  384,  4,  64, 0),    # few channels, many filters; a window mostly of halo
     (1, 130, 20, 768,  9,  2,  8),    # channels two past 4 x 32, three tiles of 256 exactly
     (1, 64, 64,  1000, 52, 8,  204),  # most taps
+    (1, 13, 9,   66001, 7, 2,  6),    # one channel block, wide enough for the three parts, odd width
     (1, 20, 20,  3200, 52, 20, 510),  # a halo of 1020 columns
 ]
 
