@@ -207,9 +207,10 @@ int conv1d_bwd_weight_noalloc(const void* x, const void* dy, float* dw,
 int conv1d_set_variant(int variant);
 
 /* Name of the kernel the current variant setting selects for a pass
- * (conv1d_pass_t) and geometry, e.g. "smallc_mfma_bf16"; "invalid" for a bad
- * geometry, "unsupported" when a forced variant cannot run it.  The string is
- * static storage. */
+ * (conv1d_pass_t) and geometry, e.g. "smallc_mfma_bf16"; "..._split_mfma_fp32"
+ * for FP32 on the bf16 matrix instructions, every float as the sum of three
+ * bfloat16 numbers; "invalid" for a bad geometry, "unsupported" when a forced
+ * variant cannot run it.  The string is static storage. */
 const char* conv1d_kernel_name(int pass, int N, int C, int K, int W, int S, int dilation, int padding,
                                int dtype);
 

@@ -159,13 +159,28 @@ int run_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws,
     return e == hipSuccess ? CONV1D_OK : CONV1D_EHIP;
 }
 
-const char* family_name(int fam, int bf16, bool wgrad) {
+// split: the family's FP32 kernels on the bf16 matrix instructions
+const char* family_name(int fam, int bf16, bool wgrad, bool split) {
     switch (fam) {
         case CONV1D_VARIANT_GENERIC: return bf16 ? (wgrad ? "generic_wgrad_bf16" : "generic_fma_bf16") : (wgrad ? "generic_wgrad_fp32" : "generic_fma_fp32");
-        case CONV1D_VARIANT_SMALLC: return bf16 ? (wgrad ? "smallc_wgrad_mfma_bf16" : "smallc_mfma_bf16") : (wgrad ? "smallc_wgrad_mfma_fp32" : "smallc_mfma_fp32");
-        case CONV1D_VARIANT_IGEMM: return bf16 ? (wgrad ? "igemm_wgrad_mfma_bf16" : "igemm_mfma_bf16") : (wgrad ? "igemm_wgrad_mfma_fp32" : "igemm_mfma_fp32");
+        case CONV1D_VARIANT_SMALLC:
+            if (split) return wgrad ? "smallc_wgrad_split_mfma_fp32" : "smallc_split_mfma_fp32";
+            return bf16 ? (wgrad ? "smallc_wgrad_mfma_bf16" : "smallc_mfma_bf16") : (wgrad ? "smallc_wgrad_mfma_fp32" : "smallc_mfma_fp32");
+        case CONV1D_VARIANT_IGEMM:
+            if (split) return wgrad ? "igemm_wgrad_split_mfma_fp32" : "igemm_split_mfma_fp32";
+            return bf16 ? (wgrad ? "igemm_wgrad_mfma_bf16" : "igemm_mfma_bf16") : (wgrad ? "igemm_wgrad_mfma_fp32" : "igemm_mfma_fp32");
         default: return "unsupported";
     }
+}
+
+const char* corr_name(const CorrProblem& p) {
+    const int fam = pick_corr(p);
+    return family_name(fam, p.bf16, false, fam == CONV1D_VARIANT_SMALLC ? smallc_corr_is_split(p) : fam == CONV1D_VARIANT_IGEMM && igemm_corr_is_split(p));
+}
+
+const char* wgrad_name(const WgradProblem& p) {
+    const int fam = pick_wgrad(p);
+    return family_name(fam, p.bf16, true, fam == CONV1D_VARIANT_SMALLC ? smallc_wgrad_is_split(p) : fam == CONV1D_VARIANT_IGEMM && igemm_wgrad_is_split(p));
 }
 
 }  // namespace
@@ -306,9 +321,9 @@ const char* conv1d_kernel_name(int pass, int N, int C, int K, int W, int S, int 
     if ((dtype != CONV1D_FP32 && dtype != CONV1D_BF16) || !make_geom(N, C, K, W, S, dilation, padding, &g)) return "invalid";
     const int bf16 = dtype == CONV1D_BF16;
     switch (pass) {
-        case CONV1D_PASS_FWD: return family_name(pick_corr(fwd_problem(g, nullptr, nullptr, nullptr, bf16)), bf16, false);
-        case CONV1D_PASS_BWD_DATA: return family_name(pick_corr(bwd_data_problem(g, nullptr, nullptr, nullptr, bf16)), bf16, false);
-        case CONV1D_PASS_BWD_WEIGHT: return family_name(pick_wgrad(wgrad_problem(g, nullptr, nullptr, nullptr, nullptr, 0, bf16)), bf16, true);
+        case CONV1D_PASS_FWD: return corr_name(fwd_problem(g, nullptr, nullptr, nullptr, bf16));
+        case CONV1D_PASS_BWD_DATA: return corr_name(bwd_data_problem(g, nullptr, nullptr, nullptr, bf16));
+        case CONV1D_PASS_BWD_WEIGHT: return wgrad_name(wgrad_problem(g, nullptr, nullptr, nullptr, nullptr, 0, bf16));
         default: return "invalid";
     }
 }

@@ -103,6 +103,8 @@ bool igemm_corr_supported(const CorrProblem& p) {
     return !(p.epi.out_bf16 && accumulates(r));
 }
 
+bool igemm_corr_is_split(const CorrProblem& p) { return corr_route(p) == CorrRoute::kF32Split; }
+
 hipError_t igemm_corr_launch(const CorrProblem& p, hipStream_t st) {
     if (!igemm_corr_supported(p)) return hipErrorInvalidValue;
     const CorrRoute route = corr_route(p);
@@ -175,6 +177,11 @@ size_t igemm_wgrad_workspace(const WgradProblem& p) {
     if (p.bf16 && blocked_bf16_wgrad_supported(p)) return blocked_bf16_wgrad_workspace(p);
     if (fp32_pairs_in_one_launch(p)) return smallc_wgrad_f32_blocks_workspace(p);
     return smallc_wgrad_workspace(wgrad_block(p, 0, 0));
+}
+
+bool igemm_wgrad_is_split(const WgradProblem& p) {
+    if (p.bf16) return false;
+    return fp32_pairs_in_one_launch(p) ? split_f32_wgrad_supported(p) : smallc_wgrad_is_split(wgrad_block(p, 0, 0));
 }
 
 hipError_t igemm_wgrad_launch(const WgradProblem& p, hipStream_t st) {

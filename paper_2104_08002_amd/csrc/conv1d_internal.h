@@ -86,6 +86,9 @@ hipError_t smallc_corr_launch(const CorrProblem& p, hipStream_t st);
 bool smallc_wgrad_supported(const WgradProblem& p);
 size_t smallc_wgrad_workspace(const WgradProblem& p);
 hipError_t smallc_wgrad_launch(const WgradProblem& p, hipStream_t st);
+// whether the launch takes the FP32 kernels on the bf16 matrix instructions (split_f32_*)
+bool smallc_corr_is_split(const CorrProblem& p);
+bool smallc_wgrad_is_split(const WgradProblem& p);
 
 // FP32 forward / backward-data with any R, M: filter blocks of 16 as rows of a single grid, channel blocks reduced
 // inside the kernel (needs the weights of all channel blocks of a filter block in LDS)
@@ -156,6 +159,8 @@ hipError_t igemm_corr_launch(const CorrProblem& p, hipStream_t st);
 bool igemm_wgrad_supported(const WgradProblem& p);
 size_t igemm_wgrad_workspace(const WgradProblem& p);
 hipError_t igemm_wgrad_launch(const WgradProblem& p, hipStream_t st);
+bool igemm_corr_is_split(const CorrProblem& p);
+bool igemm_wgrad_is_split(const WgradProblem& p);
 
 // ---- device helpers -------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_float(unsigned short b) {

@@ -779,6 +779,9 @@ static bool split_is_faster(const WgradProblem& p) {
     return static_cast<long>(p.N) * p.Q * p.S >= 200000 && split_f32_wgrad_supported(p);
 }
 
+bool smallc_corr_is_split(const CorrProblem& p) { return !p.bf16 && split_is_faster(p); }
+bool smallc_wgrad_is_split(const WgradProblem& p) { return !p.bf16 && split_is_faster(p); }
+
 bool smallc_corr_supported(const CorrProblem& p) {
     if (p.bf16) return smallc_bf16_corr_supported(p);
     return corr_f32_plan(p).ok;

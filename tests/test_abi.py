@@ -128,6 +128,17 @@ def test_wide_layers_dispatch_to_blocked_mfma_kernels():
     assert binding.conv1d_bwd_weight_workspace_bytes(*g, 0) == 256 * 51 * 256 * 4
 
 
+def test_fp32_kernel_names_tell_the_instruction():
+    """FP32 layers run on the FP32 matrix instruction or, in three bfloat16 parts, on the bf16 one: the name says which."""
+    name = binding.conv1d_kernel_name
+    binding.conv1d_set_variant(binding.VARIANT_AUTO)
+    assert [name(i, 8, 64, 64, 20000, 33, 4, 64, 0) for i in range(3)] == ["igemm_split_mfma_fp32"] * 2 + ["igemm_wgrad_split_mfma_fp32"]
+    assert [name(i, 16, 15, 15, 60000, 51, 8, 200, 0) for i in range(3)] == ["smallc_split_mfma_fp32"] * 2 + ["smallc_wgrad_split_mfma_fp32"]
+    assert [name(i, 2, 4, 4, 256, 5, 2, 0, 0) for i in range(3)] == ["smallc_mfma_fp32"] * 2 + ["smallc_wgrad_mfma_fp32"]
+    # three parts of a window of 2 x 2485 columns and a tile do not fit in LDS
+    assert name(0, 1, 3, 40, 30000, 3, 2485, 2485, 0) == "igemm_mfma_fp32"
+
+
 def test_plan_queries_survive_arbitrary_geometries():
     """Host logic only: the kernel-family decision and the workspace size of every pass for a few hundred seeded
     geometries (tiny and large channel counts, widths below one tile, dilations the fast families do not take).
