@@ -15,10 +15,17 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 __device__ __forceinline__ unsigned pack_hi(float lo, float hi) {  // upper halves of two floats, lo in the low half
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
 }
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {  // two floats to nearest even
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+// no float rounds past the largest bfloat16; NaN comes out as a number here and stays NaN in what is left
+__device__ __forceinline__ float within_bf16(float v) { return __builtin_amdgcn_fmed3f(v, -0x1.fep127f, 0x1.fep127f); }
 
-// v = h + m + l.  h: the upper 8 significant bits, cut off (no value overflows by it); m: the next 8, rounded to nearest
-// even, so that the products left out later (m l, l m, l l: 2^-25 of h h) have no preferred sign; l: what is left, which
-// fits 8 bits.  Exact while v is at least 2^-110 (below that l drops under bfloat16's smallest number).
+// v = h + m + l.  h and m: 8 significant bits each, rounded to nearest even; l: what is left, which fits 6 bits.
+// |m| <= 2^-8 |v| and |l| <= 2^-17 |v|, so the products left out later (m l, l m, l l) are at most 2^-24 of the whole, one
+// half unit in the last place of an FP32 product.  (With h cut off they reached 2^-22, all with the sign of the whole:
+// 2.35e-7 in a layer of equal values, x = w = 1 + 2^-7 - 2^-16; now 2.3e-10.)  The sum of the parts is exact while |v| is
+// at least 2^-110; below that the lowest bits fall under bfloat16's smallest number, 2^-133.
 struct Split8 {
     u32x4 h, m, l;
 };
@@ -27,12 +34,11 @@ __device__ __forceinline__ Split8 split8(const float (&v)[8]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float a = v[2 * i], b = v[2 * i + 1];
-        r.h[i] = pack_hi(a, b);
-        const float ra = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u);
-        const float rb = b - __uint_as_float(__float_as_uint(b) & 0xffff0000u);
-        const unsigned mm = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
-        r.m[i] = mm;
-        r.l[i] = pack_hi(ra - __uint_as_float(mm << 16), rb - __uint_as_float(mm & 0xffff0000u));
+        r.h[i] = pack_bf16(within_bf16(a), within_bf16(b));
+        const float ra = a - __uint_as_float(r.h[i] << 16);
+        const float rb = b - __uint_as_float(r.h[i] & 0xffff0000u);
+        r.m[i] = pack_bf16(ra, rb);
+        r.l[i] = pack_hi(ra - __uint_as_float(r.m[i] << 16), rb - __uint_as_float(r.m[i] & 0xffff0000u));
     }
     return r;
 }

@@ -3,9 +3,9 @@
 // v_mfma_f32_16x16x4_f32 does 1/16 of the operations per cycle that v_mfma_f32_16x16x32_bf16 does, and the FP32 passes
 // were bound by it.  Here each float is the sum of three bfloat16 numbers (conv1d_split_f32.h) and a product is the six
 // largest of their nine products, exact in the matrix unit and added in FP32: 6/16 of the FP32 matrix time.  The
-// products left out are 2^-25 of the whole with either sign, less than one FP32 rounding.  The sum of the six over
-// 32 terms is added to the running sums in FP32, so a sum of n terms is rounded n/32 times at full size where the FP32
-// instruction rounded it n/4 times: the error against 64 bits fell on every geometry measured.
+// products left out are at most 2^-24 of the whole, half a unit in the last place of an FP32 product.  The sum of the six
+// over 32 terms is added to the running sums in FP32, so a sum of n terms is rounded n/32 times at full size where the
+// FP32 instruction rounded it n/4 times.
 //
 // One workgroup: 16 FBW filters x 64 PB output columns of one sample, wave v the columns 16 PB v ..  A step is one
 // matrix instruction deep (32 = 4 lane groups x 8 channels): PL planes of 8 channels times 4/PL taps.  The input

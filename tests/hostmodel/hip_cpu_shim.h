@@ -67,6 +67,8 @@ inline long max(long a, long b) { return a > b ? a : b; }
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)
+inline float hostmodel_fmed3f(float v, float lo, float hi) { return v < lo ? lo : (v > hi ? hi : v); }
+#define __builtin_amdgcn_fmed3f(a, b, c) hostmodel_fmed3f(a, b, c)
 inline unsigned hostmodel_perm(unsigned hi, unsigned lo, unsigned sel) {
     const uint64_t v = (static_cast<uint64_t>(hi) << 32) | lo;
     unsigned r = 0;

@@ -55,3 +55,47 @@ def test_split_layers(binding, case):
     errs = check_full(oracle, wl, data, gpu_passes(wl, to_device(wl, data)))
     print(case, errs, flush=True)
     assert all(e <= TOL for e in errs.values()), errs
+
+
+# x = w = dy = v: every product leaves the same part out, with the same sign
+ADVERSE = [1.0 + 2.0 ** -7 - 2.0 ** -16, 1.2265472412109375, 1.0 + 2.0 ** -8 - 2.0 ** -17, 2.0 - 2.0 ** -9 + 2.0 ** -18]
+
+
+@pytest.mark.parametrize("v", ADVERSE)
+def test_products_left_out(binding, v):
+    """32 equal products per output, one step of the matrix instruction.  The parts leave at most 2^-24 of each product
+    out, the instruction cuts the sum of the large parts off at 2^-23 of itself and the five smaller sums at 2^-8 of that."""
+    import torch
+
+    bound = 2.0 ** -24 + 2.0 ** -23 * (1 + 5 * 2.0 ** -8)
+    x = torch.full((1, 32, 400), v, device="cuda")
+    w = torch.full((32, 32, 1), v, device="cuda")
+    exact = 32 * float(x[0, 0, 0]) ** 2
+    for i, name in enumerate(("igemm_split_mfma_fp32", "igemm_split_mfma_fp32", "igemm_wgrad_split_mfma_fp32")):
+        assert binding.conv1d_kernel_name(i, 1, 32, 32, 400 if i < 2 else 32, 1, 1, 0, 0) == name
+    y = binding.conv1d_fwd(x, w, 1, 0)
+    dx = binding.conv1d_bwd_data(x, w, 400, 1, 0)
+    dw = binding.conv1d_bwd_weight(x[:, :, :32].contiguous(), x[:, :, :32].contiguous(), 1, 1, 0)
+    for what, t in (("fwd", y), ("bwd_data", dx), ("bwd_weight", dw)):
+        err = float(((t.double() - exact) / exact).abs().max())
+        print(v, what, err, flush=True)
+        assert err <= bound, (what, err, bound)
+
+
+def test_largest_and_smallest_floats(binding):
+    """One weight of 1 per filter: the output is the input, up to the largest float (no part overflows) and down to
+    2^-110; below that the parts lose what lies under 2^-133."""
+    import torch
+
+    w = torch.zeros((32, 32, 1), device="cuda")
+    w[torch.arange(32), torch.arange(32), 0] = 1.0
+    big = torch.tensor([3.4028234663852886e38, 3.3961775292304601e38, 3.39e38, -3.4028234663852886e38, 1.0], device="cuda")
+    x = big.repeat(100)[:500].expand(1, 32, 500).contiguous()
+    assert binding.conv1d_kernel_name(0, 1, 32, 32, 500, 1, 1, 0, 0) == "igemm_split_mfma_fp32"
+    assert torch.equal(binding.conv1d_fwd(x, w, 1, 0), x)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    m = 1 + torch.rand((1, 32, 500), generator=gen, device="cuda")
+    x = torch.ldexp(m, torch.tensor(-110, device="cuda"))
+    assert torch.equal(binding.conv1d_fwd(x, w, 1, 0), x)
+    x = torch.ldexp(m, torch.tensor(-120, device="cuda"))
+    assert float((binding.conv1d_fwd(x, w, 1, 0).double() - x.double()).abs().max()) < 2.0 ** -133
