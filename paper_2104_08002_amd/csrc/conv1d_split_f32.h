@@ -47,6 +47,12 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// Shortest sum taken, one matrix instruction deep.  Its additions cut off, once per step, where the FP32 instruction rounds
+// to nearest, once per four products.  Norm of the error against 64 bits, FP32 instruction and three parts: normal values
+// 2.5e-8 and 3.6e-8 (1 product), 5.6 and 3.1 (8), 10 and 3.8 (32); tracks of 80 % zeros 2.5 and 3.6 (1), 3.3 and 3.4 (8),
+// 5.1 and 3.5 (32).
+constexpr long kMinTerms = 32;
+
 // The six products of a step start from zero, smallest first, and their sum is added to the running one in an ordinary
 // FP32 addition.  Chained through the running sums themselves the matrix instruction's additions lost more than the
 // FP32 instruction's did: error of a weight gradient of 3.4 million terms against 64 bits 2.9e-5 so, 8.2e-6 with

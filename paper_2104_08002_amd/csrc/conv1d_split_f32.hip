@@ -199,7 +199,7 @@ struct Plan {
 
 Plan make_plan(const CorrProblem& p) {
     Plan best{};
-    if (p.bf16 || p.accumulate || p.epi.out_bf16 || p.tail.ws) return best;
+    if (p.bf16 || p.accumulate || p.epi.out_bf16 || p.tail.ws || static_cast<long>(p.R) * p.S < kMinTerms) return best;
     const int mb = cdiv(p.M, 16);
     double best_cost = 0;
     for (int fbw = 1; fbw <= 4; ++fbw) {

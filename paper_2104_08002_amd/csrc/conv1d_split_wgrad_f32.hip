@@ -275,7 +275,7 @@ constexpr int kShapes[][2] = {{1, 3}, {1, 5}, {1, 7}, {1, 9}, {1, 13}, {2, 2}, {
 
 Plan make_plan(const WgradProblem& p) {
     Plan best{};
-    if (p.bf16 || p.dw_sc != p.S) return best;
+    if (p.bf16 || p.dw_sc != p.S || static_cast<long>(p.N) * p.Q < kMinTerms) return best;
     const size_t wsb = smallc_wgrad_f32_blocks_workspace(p);  // the partial tiles take no more than that kernel's
     if (wsb == 0) return best;
     const int cblocks = cdiv(p.C, 16), kblocks = cdiv(p.K, 16);

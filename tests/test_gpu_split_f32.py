@@ -82,6 +82,34 @@ def test_products_left_out(binding, v):
         assert err <= bound, (what, err, bound)
 
 
+# channels and taps of the forward pass (K = 40), columns of the weight gradient
+SHORT = [(1, 1), (2, 1), (1, 3), (4, 5), (31, 1)]
+
+
+@pytest.mark.parametrize("case", SHORT, ids=lambda c: "x".join(map(str, c)))
+def test_short_sums_are_rounded_as_fp32(binding, case):
+    """Sums of fewer than 32 products: one rounding to nearest a product, n 2^-24 of sum|products|, as FP32 arithmetic has
+    it (a single product is the correctly rounded one)."""
+    import torch
+
+    import oracle
+
+    oracle.build()
+    C, S = case
+    n = C * S
+    wl = inputs.scaled(inputs.TINY, name=f"short_{C}_{S}", N=2, C=C, K=40, W=3000, S=S, d=2, P=0, x_dist="normal",
+                       w_dist="normal_fan", dy_dist="normal", seed=inputs.BASE_SEED + 7500 + n)
+    assert binding.conv1d_kernel_name(0, *wl.geometry(), 0) == "igemm_mfma_fp32"
+    data = inputs.make_inputs(wl)
+    errs = check_full(oracle, wl, data, gpu_passes(wl, to_device(wl, data), passes=("fwd",)), passes=("fwd",))
+    wl = inputs.scaled(wl, name=f"short_wgrad_{n}", N=1, C=40, W=n + 2 * (S - 1))
+    assert wl.Q == n and binding.conv1d_kernel_name(2, *wl.geometry(), 0) == "igemm_wgrad_mfma_fp32"
+    data = inputs.make_inputs(wl)
+    errs.update(check_full(oracle, wl, data, gpu_passes(wl, to_device(wl, data), passes=("bwd_weight",)), passes=("bwd_weight",)))
+    print(case, errs, flush=True)
+    assert all(e <= n * 2.0 ** -24 * (1 + 2.0 ** -20) for e in errs.values()), errs
+
+
 def test_largest_and_smallest_floats(binding):
     """One weight of 1 per filter: the output is the input, up to the largest float (no part overflows) and down to
     2^-110; below that the parts lose what lies under 2^-133."""
