@@ -197,9 +197,37 @@ struct Plan {
     long grid;
 };
 
+// Planes per step (1 << result), which decides the order of an output's sum: from what a sample is, not from how many there
+// are, so that a sample's result does not depend on its batch.  The least of matrix time plus what steps and windows cost
+// beside it over the tiles; workgroups that share a CU hide half of the latter.  -1: no tile fits.
+int planes_shift(const CorrProblem& p) {
+    int best = -1;
+    double best_cost = 0;
+    for (int fbw = 1; fbw <= 4; ++fbw) {
+        for (int pb = 4; pb <= 8; ++pb) {
+            if (pb == 7 || fbw * pb > 20) continue;
+            const double tiles = static_cast<double>(cdiv(p.Wout, 64 * pb)) * cdiv(cdiv(p.M, 16), fbw);
+            for (int sh = 0; sh <= 2; ++sh) {
+                const int tp = 4 >> sh, nsteps = cdiv(p.S, tp), nstages = cdiv(p.R, 8 << sh);
+                const long wlen = 64L * pb + (static_cast<long>(nsteps) * tp - 1) * p.d;
+                const size_t lds = (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * fbw * 192) * 16;
+                if (wlen > 16384 || lds > kLdsAll) continue;
+                const double beside = nsteps * 600.0 + 1000.0 + (wlen << sh) * 2.0;
+                const double cost = tiles * nstages * (nsteps * 96.0 * fbw * pb + (lds <= kLdsHalf ? 0.5 : 1.0) * beside);
+                if (best >= 0 && cost >= best_cost) continue;
+                best_cost = cost;
+                best = sh;
+            }
+        }
+    }
+    return best;
+}
+
 Plan make_plan(const CorrProblem& p) {
     Plan best{};
     if (p.bf16 || p.accumulate || p.epi.out_bf16 || p.tail.ws || static_cast<long>(p.R) * p.S < kMinTerms) return best;
+    const int sh = planes_shift(p);
+    if (sh < 0) return best;
     const int mb = cdiv(p.M, 16);
     double best_cost = 0;
     for (int fbw = 1; fbw <= 4; ++fbw) {
@@ -208,39 +236,37 @@ Plan make_plan(const CorrProblem& p) {
             const int qtiles = cdiv(p.Wout, 64 * pb), fgroups = cdiv(mb, fbw);
             const long grid = static_cast<long>(p.N) * qtiles * fgroups;
             if (grid > 0x7fffffffL / kThreads) continue;
-            for (int sh = 0; sh <= 2; ++sh) {
-                const int tp = 4 >> sh, nsteps = cdiv(p.S, tp), nstages = cdiv(p.R, 8 << sh);
-                const long wlen = 64L * pb + (static_cast<long>(nsteps) * tp - 1) * p.d;
-                const size_t lds = (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * fbw * 192) * 16;
-                if (wlen > 16384 || lds > kLdsAll) continue;
-                // cycles of the busiest CU: matrix time of its workgroups, plus what a step and a window cost beside it;
-                // a workgroup alone on its CU hides none of that
-                const double staging = nsteps * 400.0 + 3000.0 + (wlen << sh) * 6.0;
-                const double mm = static_cast<double>(nsteps) * fbw * pb * 96;
-                const long per_cu = (grid + 255) / 256;
-                const bool shared = lds <= kLdsHalf && per_cu > 1;
-                const double lds_reads = static_cast<double>(nsteps) * (3 * pb + 3 * fbw) * 4 * 8;
-                const double busy = mm > lds_reads ? mm : lds_reads;
-                const double cost = nstages * per_cu * (busy + (shared ? 0.3 : 1.0) * staging);
-                if (best.ok && cost >= best_cost) continue;
-                best_cost = cost;
-                best.ok = true;
-                best.fbw = fbw;
-                best.pb = pb;
-                best.lds = lds;
-                best.grid = grid;
-                SpArgs& a = best.a;
-                a.in = static_cast<const float*>(p.in);
-                a.wt = static_cast<const float*>(p.wt);
-                a.out = p.out;
-                a.epi = p.epi;
-                a.R = p.R; a.M = p.M; a.Win = p.Win; a.Wout = p.Wout; a.S = p.S; a.d = p.d; a.P = p.P;
-                a.w_sm = p.w_sm; a.w_sr = p.w_sr; a.in_sn = p.in_sn; a.out_sn = p.out_sn;
-                a.w_s0 = p.w_s0; a.w_ss = p.w_ss;
-                a.pl_sh = sh; a.nstages = nstages; a.nsteps = nsteps; a.wlen = static_cast<int>(wlen);
-                a.qtiles = qtiles; a.fgroups = fgroups;
-                a.vec = p.Wout % 4 == 0 && p.out_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15) == 0;
-            }
+            const int tp = 4 >> sh, nsteps = cdiv(p.S, tp), nstages = cdiv(p.R, 8 << sh);
+            const long wlen = 64L * pb + (static_cast<long>(nsteps) * tp - 1) * p.d;
+            const size_t lds = (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * fbw * 192) * 16;
+            if (wlen > 16384 || lds > kLdsAll) continue;
+            // cycles of the busiest CU: matrix time of its workgroups, plus what a step and a window cost beside it;
+            // a workgroup alone on its CU hides none of that
+            const double staging = nsteps * 400.0 + 3000.0 + (wlen << sh) * 6.0;
+            const double mm = static_cast<double>(nsteps) * fbw * pb * 96;
+            const long per_cu = (grid + 255) / 256;
+            const bool shared = lds <= kLdsHalf && per_cu > 1;
+            const double lds_reads = static_cast<double>(nsteps) * (3 * pb + 3 * fbw) * 4 * 8;
+            const double busy = mm > lds_reads ? mm : lds_reads;
+            const double cost = nstages * per_cu * (busy + (shared ? 0.3 : 1.0) * staging);
+            if (best.ok && cost >= best_cost) continue;
+            best_cost = cost;
+            best.ok = true;
+            best.fbw = fbw;
+            best.pb = pb;
+            best.lds = lds;
+            best.grid = grid;
+            SpArgs& a = best.a;
+            a.in = static_cast<const float*>(p.in);
+            a.wt = static_cast<const float*>(p.wt);
+            a.out = p.out;
+            a.epi = p.epi;
+            a.R = p.R; a.M = p.M; a.Win = p.Win; a.Wout = p.Wout; a.S = p.S; a.d = p.d; a.P = p.P;
+            a.w_sm = p.w_sm; a.w_sr = p.w_sr; a.in_sn = p.in_sn; a.out_sn = p.out_sn;
+            a.w_s0 = p.w_s0; a.w_ss = p.w_ss;
+            a.pl_sh = sh; a.nstages = nstages; a.nsteps = nsteps; a.wlen = static_cast<int>(wlen);
+            a.qtiles = qtiles; a.fgroups = fgroups;
+            a.vec = p.Wout % 4 == 0 && p.out_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15) == 0;
         }
     }
     return best;

@@ -127,3 +127,27 @@ def test_largest_and_smallest_floats(binding):
     assert torch.equal(binding.conv1d_fwd(x, w, 1, 0), x)
     x = torch.ldexp(m, torch.tensor(-120, device="cuda"))
     assert float((binding.conv1d_fwd(x, w, 1, 0).double() - x.double()).abs().max()) < 2.0 ** -133
+
+
+# layers of more than 16 channels or filters
+BATCH = [(64, 64, 4000, 5, 2), (100, 100, 1000, 9, 1), (40, 24, 1300, 7, 3), (17, 33, 2000, 15, 4)]
+
+
+@pytest.mark.parametrize("case", BATCH, ids=lambda c: "x".join(map(str, c)))
+def test_a_sample_does_not_depend_on_its_batch(binding, case):
+    """Forward and backward-data of a sample give the same bits alone and among others: tiles follow the size of the
+    launch, the order of the sums must not."""
+    import torch
+
+    C, K, W, S, d = case
+    P = (S - 1) * d // 2
+    Q = W + 2 * P - (S - 1) * d
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn((56, C, W), generator=gen, device="cuda")
+    dy = torch.randn((56, K, Q), generator=gen, device="cuda")
+    w = torch.randn((K, C, S), generator=gen, device="cuda")
+    y1 = torch.cat([binding.conv1d_fwd(x[i:i + 1].contiguous(), w, d, P) for i in (0, 1)])
+    dx1 = torch.cat([binding.conv1d_bwd_data(dy[i:i + 1].contiguous(), w, W, d, P) for i in (0, 1)])
+    for n in (2, 3, 5, 8, 13, 16, 21, 33, 40, 48, 56):
+        assert torch.equal(binding.conv1d_fwd(x[:n], w, d, P)[:2], y1), n
+        assert torch.equal(binding.conv1d_bwd_data(dy[:n], w, W, d, P)[:2], dx1), n
