@@ -149,6 +149,14 @@ hipError_t igemm_stream_bf16_corr_launch(const CorrProblem& p, hipStream_t st);
 // FP32 forward / backward-data on the bf16 matrix instructions: every float as the sum of three bfloat16 numbers
 bool split_f32_corr_supported(const CorrProblem& p);
 hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st);
+// what such a launch would take (the tests choose their geometries by it): filter blocks of 16 per workgroup; column blocks
+// of 64 per workgroup, or taps per wave; planes of 8 channels per step, or units of the longest strip; workgroups
+struct SplitTile {
+    int filter_blocks, columns_or_taps, planes_or_units;
+    long grid;
+};
+bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t);
+bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
 // FP32 backward-weight the same way; workspace and second stage of smallc_wgrad_f32_blocks_*
 bool split_f32_wgrad_supported(const WgradProblem& p);
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st);

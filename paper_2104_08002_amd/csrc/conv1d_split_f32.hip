@@ -11,8 +11,7 @@
 // matrix instruction deep (32 = 4 lane groups x 8 channels): PL planes of 8 channels times 4/PL taps.  The input
 // window of PL planes sits in LDS as [part][plane][position] slots of 8 channels, so any dilation is a slot offset; the
 // weights of one step are gathered from (K, C, S), split and written to LDS one step ahead, double-buffered, one
-// barrier per step.  Workgroups are kept to half the LDS and 256 registers: two share a CU, and one multiplies while
-// the other stages.
+// barrier per step; the waves take turns at that.  Workgroups that share a CU multiply while others stage.
 #include "conv1d_split_f32.h"
 
 namespace conv1d {
@@ -20,7 +19,7 @@ namespace {
 using namespace sp;
 
 constexpr int kThreads = 256;
-constexpr size_t kLdsHalf = 80 * 1024, kLdsAll = 160 * 1024;
+constexpr size_t kLdsAll = 160 * 1024;
 
 struct SpArgs {
     const float* in;
@@ -36,7 +35,8 @@ struct SpArgs {
 template <int FBW, int PB>
 __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
     extern __shared__ u32x4 lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int PL = 1 << a.pl_sh, TP = 4 >> a.pl_sh;
     const int part = PL * a.wlen;
     u32x4* xs = lds;
@@ -49,33 +49,46 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
     const int q0 = qt * (64 * PB), m0 = fg * (16 * FBW);
     const float* inb = a.in + n * a.in_sn;
 
-    // the weight entry of this thread: filter em, lane group g's plane and tap of the step
-    const int em = m0 + (tid >> 6) * 16 + l16;
-    const bool has_entry = tid < FBW * 64;
+    // Weight entries: FBW waves hold one step's, the other waves those of the steps after it (NG groups of waves in turn),
+    // so that a group's loads have NG steps to arrive.  With all of them one step ahead a step of a workgroup alone on its
+    // CU took as long as the loads, about 1 us (C = K = 64, S = 33, d = 4, up to 16000 columns: 68 us a pass).
+    constexpr int NG = 4 / FBW;
+    const bool has_entry = wave < NG * FBW;
+    const int ef = wave % FBW, em = m0 + ef * 16 + l16;  // filter of this thread's entry; lane group g has plane and tap
     const float* wrow = a.wt + min(em, a.M - 1) * a.w_sm + a.w_s0;
     const int eplane = g & (PL - 1), etap = g >> a.pl_sh;
+    const int total = a.nstages * a.nsteps;
+    int due = wave / FBW;  // step, counted over all stages, of the entry in wv
+    int wstage = 0, wstep = due;
     float wv[8];
     int cleft = 0;
-    auto request = [&](int stage, int step) {
-        if (!has_entry) return;
-        const int tap = step * TP + etap, c = 8 * (stage * PL + eplane);
+    auto request = [&] {
+        if (!has_entry || due >= total) return;
+        while (wstep >= a.nsteps) {
+            wstep -= a.nsteps;
+            ++wstage;
+        }
+        const int tap = wstep * TP + etap, c = 8 * (wstage * PL + eplane);
         const float* p = wrow + static_cast<long>(min(tap, a.S - 1)) * a.w_ss;
         cleft = (em < a.M && tap < a.S) ? a.R - c : 0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) wv[j] = p[min(c + j, a.R - 1) * a.w_sr];
     };
-    // channels, taps and filters the layer does not have count as zero; put right here, so that nothing waits for the
-    // loads before the products of a step are done
-    auto park = [&](int buf) {
-        if (!has_entry) return;
+    // entry of the given step, if this wave has it.  Channels, taps and filters the layer does not have count as zero; put
+    // right here, so that nothing waits for the loads before the products of a step are done
+    auto park = [&](int step, int buf) {
+        if (!has_entry || due != step || step >= total) return;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             if (j >= cleft) wv[j] = 0.f;
         const Split8 s = split8(wv);
-        u32x4* e = ws + (buf * FBW + (tid >> 6)) * 192 + lane;
+        u32x4* e = ws + (buf * FBW + ef) * 192 + lane;
         e[0] = s.h;
         e[64] = s.m;
         e[128] = s.l;
+        due += NG;
+        wstep += NG;
+        request();
     };
 
     f32x4 acc[PB][FBW];
@@ -84,8 +97,8 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
 #pragma unroll
         for (int f = 0; f < FBW; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    request(0, 0);
-    int buf = 0;
+    request();
+    int buf = 0, next = 1;  // step after the current one, counted over all stages
     const int rd0 = (g & (PL - 1)) * a.wlen + (g >> a.pl_sh) * a.d + wave * (16 * PB) + l16;
     for (int stage = 0; stage < a.nstages; ++stage) {
         const int col0 = q0 - a.P;
@@ -117,12 +130,10 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
                 }
             }
         }
-        if (stage == 0) park(0);
+        if (stage == 0) park(0, 0);
         __syncthreads();
         int rd = rd0;
-        for (int step = 0; step < a.nsteps; ++step, rd += TP * a.d) {
-            const bool more = step + 1 < a.nsteps || stage + 1 < a.nstages;
-            if (more) request(step + 1 < a.nsteps ? stage : stage + 1, step + 1 < a.nsteps ? step + 1 : 0);
+        for (int step = 0; step < a.nsteps; ++step, ++next, rd += TP * a.d) {
             u32x4 w[FBW][3];
 #pragma unroll
             for (int f = 0; f < FBW; ++f)
@@ -139,6 +150,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
                         for (int i = 0; i < 3; ++i) xr[(t0 / U) & 1][u][i] = xs[i * part + rd + 16 * (t0 + u)];
             };
             read(0);
+            if constexpr (NG > 1) park(next, buf ^ 1);  // under the latency of the reads; with one group the loads are not here yet
 #pragma unroll
             for (int t0 = 0; t0 < PB; t0 += U) {
                 if (t0 + U < PB) read(t0 + U);
@@ -161,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
                 __builtin_amdgcn_sched_barrier(0);
             }
             buf ^= 1;
-            if (more) park(buf);
+            if constexpr (NG == 1) park(next, buf);
             __syncthreads();
         }
     }
@@ -189,35 +201,73 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
     }
 }
 
+struct Tile {
+    int fbw, pb;
+};
+// sums, weights and inputs within 256 registers
+constexpr Tile kTiles[] = {{1, 1}, {1, 2}, {1, 4}, {1, 5}, {1, 6}, {1, 8}, {2, 4}, {2, 5}, {2, 6}, {2, 8}, {3, 4}, {3, 5}, {3, 6}, {4, 4}, {4, 5}};
+
 struct Plan {
     bool ok;
-    int fbw, pb;
+    Tile tile;
     SpArgs a;
     size_t lds;
     long grid;
 };
 
+// A tile with 1 << sh planes per step on this layer, and its time as a model of cycles: `alone`, a workgroup with its CU
+// to itself, which is a chain of reads, products and barriers; `busy`, what it takes of the pipes it shares with others,
+// most of it the gather of weights, whose 64 lanes fall on 64 cache lines.  The constants are a fit to the forward times
+// of these tiles on 22 layers (C, K 4 ... 256, 1 ... 51 taps) at 500 ... 2.4 million columns; tile and planes picked by it
+// are within 21 % of the fastest everywhere, 2 % on average.  Small launches get narrow tiles: 64 columns take 36 us where
+// 256 take 49 on 2000 columns of C = K = 64, S = 33, d = 4 (FP32 instruction 61 us).
+struct Fit {
+    bool ok;
+    int nsteps, nstages, resident;
+    long wlen, per_sample;  // workgroups of a sample
+    size_t lds;
+    double alone, busy;
+    double time(long grid) const {
+        const long slots = 256L * resident, full = (grid - 1) / slots, last = (grid - full * slots + 255) / 256;
+        const double whole = alone > resident * busy ? alone : resident * busy;
+        return full * whole + (alone > last * busy ? alone : last * busy);
+    }
+};
+Fit fit(const CorrProblem& p, Tile t, int sh) {
+    Fit f{};
+    const int tp = 4 >> sh;
+    f.nsteps = cdiv(p.S, tp);
+    f.nstages = cdiv(p.R, 8 << sh);
+    f.wlen = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
+    f.lds = (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16;
+    if (f.wlen > 16384 || f.lds > kLdsAll) return f;
+    const int by_lds = static_cast<int>(kLdsAll / f.lds), by_regs = 512 / (94 + 12 * t.fbw + 4 * t.fbw * t.pb);
+    f.resident = by_lds < by_regs ? by_lds : by_regs;
+    if (f.resident < 1) f.resident = 1;
+    f.per_sample = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * cdiv(cdiv(p.M, 16), t.fbw);
+    const double window = static_cast<double>(f.wlen << sh);
+    const double mm = 150.0 * t.fbw * t.pb, loads = 610.0 * t.fbw + 31.0 * (t.fbw + t.pb);
+    f.alone = f.nstages * (f.nsteps * (240.0 + 350.0 * t.fbw + (22.0 + 100.0 * t.fbw) * t.pb + (t.fbw > 2 ? 1000.0 : 0.0)) + 6 * window);
+    f.busy = f.nstages * (f.nsteps * (mm > loads ? mm : loads) + 3.6 * window);
+    f.ok = true;
+    return f;
+}
+
 // Planes per step (1 << result), which decides the order of an output's sum: from what a sample is, not from how many there
 // are, so that a sample's result does not depend on its batch.  The least of matrix time plus what steps and windows cost
-// beside it over the tiles; workgroups that share a CU hide half of the latter.  -1: no tile fits.
+// beside it over the tiles of 256 columns and more; workgroups that share a CU hide half of the latter.  -1: none fits.
 int planes_shift(const CorrProblem& p) {
     int best = -1;
     double best_cost = 0;
-    for (int fbw = 1; fbw <= 4; ++fbw) {
-        for (int pb = 4; pb <= 8; ++pb) {
-            if (pb == 7 || fbw * pb > 20) continue;
-            const double tiles = static_cast<double>(cdiv(p.Wout, 64 * pb)) * cdiv(cdiv(p.M, 16), fbw);
-            for (int sh = 0; sh <= 2; ++sh) {
-                const int tp = 4 >> sh, nsteps = cdiv(p.S, tp), nstages = cdiv(p.R, 8 << sh);
-                const long wlen = 64L * pb + (static_cast<long>(nsteps) * tp - 1) * p.d;
-                const size_t lds = (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * fbw * 192) * 16;
-                if (wlen > 16384 || lds > kLdsAll) continue;
-                const double beside = nsteps * 600.0 + 1000.0 + (wlen << sh) * 2.0;
-                const double cost = tiles * nstages * (nsteps * 96.0 * fbw * pb + (lds <= kLdsHalf ? 0.5 : 1.0) * beside);
-                if (best >= 0 && cost >= best_cost) continue;
-                best_cost = cost;
-                best = sh;
-            }
+    for (const Tile t : kTiles) {
+        for (int sh = 0; sh <= 2; ++sh) {
+            const Fit f = fit(p, t, sh);
+            if (!f.ok || t.pb < 4) continue;
+            const double beside = f.nsteps * 600.0 + 1000.0 + (f.wlen << sh) * 2.0;
+            const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * f.lds <= kLdsAll ? 0.5 : 1.0) * beside);
+            if (best >= 0 && cost >= best_cost) continue;
+            best_cost = cost;
+            best = sh;
         }
     }
     return best;
@@ -228,47 +278,36 @@ Plan make_plan(const CorrProblem& p) {
     if (p.bf16 || p.accumulate || p.epi.out_bf16 || p.tail.ws || static_cast<long>(p.R) * p.S < kMinTerms) return best;
     const int sh = planes_shift(p);
     if (sh < 0) return best;
-    const int mb = cdiv(p.M, 16);
-    double best_cost = 0;
-    for (int fbw = 1; fbw <= 4; ++fbw) {
-        for (int pb = 4; pb <= 8; ++pb) {
-            if (pb == 7 || fbw * pb > 20) continue;  // sums, weights and inputs within 256 registers
-            const int qtiles = cdiv(p.Wout, 64 * pb), fgroups = cdiv(mb, fbw);
-            const long grid = static_cast<long>(p.N) * qtiles * fgroups;
-            if (grid > 0x7fffffffL / kThreads) continue;
-            const int tp = 4 >> sh, nsteps = cdiv(p.S, tp), nstages = cdiv(p.R, 8 << sh);
-            const long wlen = 64L * pb + (static_cast<long>(nsteps) * tp - 1) * p.d;
-            const size_t lds = (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * fbw * 192) * 16;
-            if (wlen > 16384 || lds > kLdsAll) continue;
-            // cycles of the busiest CU: matrix time of its workgroups, plus what a step and a window cost beside it;
-            // a workgroup alone on its CU hides none of that
-            const double staging = nsteps * 400.0 + 3000.0 + (wlen << sh) * 6.0;
-            const double mm = static_cast<double>(nsteps) * fbw * pb * 96;
-            const long per_cu = (grid + 255) / 256;
-            const bool shared = lds <= kLdsHalf && per_cu > 1;
-            const double lds_reads = static_cast<double>(nsteps) * (3 * pb + 3 * fbw) * 4 * 8;
-            const double busy = mm > lds_reads ? mm : lds_reads;
-            const double cost = nstages * per_cu * (busy + (shared ? 0.3 : 1.0) * staging);
-            if (best.ok && cost >= best_cost) continue;
-            best_cost = cost;
-            best.ok = true;
-            best.fbw = fbw;
-            best.pb = pb;
-            best.lds = lds;
-            best.grid = grid;
-            SpArgs& a = best.a;
-            a.in = static_cast<const float*>(p.in);
-            a.wt = static_cast<const float*>(p.wt);
-            a.out = p.out;
-            a.epi = p.epi;
-            a.R = p.R; a.M = p.M; a.Win = p.Win; a.Wout = p.Wout; a.S = p.S; a.d = p.d; a.P = p.P;
-            a.w_sm = p.w_sm; a.w_sr = p.w_sr; a.in_sn = p.in_sn; a.out_sn = p.out_sn;
-            a.w_s0 = p.w_s0; a.w_ss = p.w_ss;
-            a.pl_sh = sh; a.nstages = nstages; a.nsteps = nsteps; a.wlen = static_cast<int>(wlen);
-            a.qtiles = qtiles; a.fgroups = fgroups;
-            a.vec = p.Wout % 4 == 0 && p.out_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15) == 0;
-        }
+    Fit bf{};
+    double best_time = 0;
+    for (const Tile t : kTiles) {
+        const Fit f = fit(p, t, sh);
+        if (!f.ok) continue;
+        const long grid = p.N * f.per_sample;
+        if (grid > 0x7fffffffL / kThreads) continue;
+        const double time = f.time(grid);
+        if (best.ok && time >= best_time) continue;
+        best.ok = true;
+        best_time = time;
+        best.tile = t;
+        best.grid = grid;
+        best.a.pl_sh = sh;
+        bf = f;
     }
+    if (!best.ok) return best;
+    best.lds = bf.lds;
+    SpArgs& a = best.a;
+    a.in = static_cast<const float*>(p.in);
+    a.wt = static_cast<const float*>(p.wt);
+    a.out = p.out;
+    a.epi = p.epi;
+    a.R = p.R; a.M = p.M; a.Win = p.Win; a.Wout = p.Wout; a.S = p.S; a.d = p.d; a.P = p.P;
+    a.w_sm = p.w_sm; a.w_sr = p.w_sr; a.in_sn = p.in_sn; a.out_sn = p.out_sn;
+    a.w_s0 = p.w_s0; a.w_ss = p.w_ss;
+    a.nstages = bf.nstages; a.nsteps = bf.nsteps; a.wlen = static_cast<int>(bf.wlen);
+    a.qtiles = cdiv(p.Wout, 64 * best.tile.pb);
+    a.fgroups = cdiv(cdiv(p.M, 16), best.tile.fbw);
+    a.vec = p.Wout % 4 == 0 && p.out_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15) == 0;
     return best;
 }
 
@@ -280,35 +319,27 @@ hipError_t run(const Plan& pl, hipStream_t st) {
     return launch_kernel(kern, dim3(static_cast<unsigned>(pl.grid)), dim3(kThreads), pl.lds, st, pl.a);
 }
 
-template <int FBW>
-hipError_t run_pb(const Plan& pl, hipStream_t st) {
-    switch (pl.pb) {
-        case 4: return run<FBW, 4>(pl, st);
-        case 5: return run<FBW, 5>(pl, st);
-        case 6:
-            if constexpr (FBW <= 3) return run<FBW, 6>(pl, st);
-            break;
-        case 8:
-            if constexpr (FBW <= 2) return run<FBW, 8>(pl, st);
-            break;
-        default: break;
-    }
-    return hipErrorInvalidValue;
+template <size_t... I>
+hipError_t run_tile(const Plan& pl, hipStream_t st, std::index_sequence<I...>) {
+    hipError_t e = hipErrorInvalidValue;
+    (void)((pl.tile.fbw == kTiles[I].fbw && pl.tile.pb == kTiles[I].pb && (e = run<kTiles[I].fbw, kTiles[I].pb>(pl, st), true)) || ...);
+    return e;
 }
 
 }  // namespace
 
 bool split_f32_corr_supported(const CorrProblem& p) { return make_plan(p).ok; }
 
+bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t) {
+    const Plan pl = make_plan(p);
+    *t = SplitTile{pl.tile.fbw, pl.tile.pb, 1 << pl.a.pl_sh, pl.grid};
+    return pl.ok;
+}
+
 hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st) {
     const Plan pl = make_plan(p);
     if (!pl.ok) return hipErrorInvalidValue;
-    switch (pl.fbw) {
-        case 1: return run_pb<1>(pl, st);
-        case 2: return run_pb<2>(pl, st);
-        case 3: return run_pb<3>(pl, st);
-        default: return run_pb<4>(pl, st);
-    }
+    return run_tile(pl, st, std::make_index_sequence<sizeof(kTiles) / sizeof(kTiles[0])>{});
 }
 
 }  // namespace conv1d

@@ -338,6 +338,12 @@ hipError_t run(const Plan& pl, hipStream_t st) {
 
 bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; }
 
+bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
+    const Plan pl = make_plan(p);
+    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
+    return pl.ok;
+}
+
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st) {
     const Plan pl = make_plan(p);
     if (!pl.ok) return hipErrorInvalidValue;

@@ -172,6 +172,28 @@ extern "C" const char* hostmodel_kernel_name(int pass, int N, int C, int K, int 
     return conv1d_kernel_name(pass, N, C, K, W, S, d, P, dtype);
 }
 
+// Tile of the FP32 kernels in three bfloat16 parts for a pass (0 forward, 1 backward-data, 2 backward-weight): t[0 .. 3] as
+// conv1d::SplitTile; returns 0 where the pass cannot run on them.
+extern "C" int hostmodel_split_tile(int pass, int N, int C, int K, int W, int S, int d, int P, long* t) {
+    const int Q = W + 2 * P - (S - 1) * d;
+    conv1d::SplitTile r{};
+    bool ok;
+    if (pass == 2) {
+        conv1d::WgradProblem p{};
+        p.N = N; p.C = C; p.K = K; p.W = W; p.Q = Q; p.S = S; p.d = d; p.P = P;
+        p.x_sn = static_cast<long>(C) * W; p.dy_sn = static_cast<long>(K) * Q; p.dw_sk = static_cast<long>(C) * S; p.dw_sc = S;
+        ok = conv1d::split_f32_wgrad_tile(p, &r);
+    } else {
+        conv1d::CorrProblem p{};
+        p.N = N; p.S = S; p.d = d;
+        p.R = pass == 0 ? C : K; p.M = pass == 0 ? K : C; p.Win = pass == 0 ? W : Q; p.Wout = pass == 0 ? Q : W;
+        p.P = pass == 0 ? P : (S - 1) * d - P;
+        ok = conv1d::split_f32_corr_tile(p, &r);
+    }
+    t[0] = r.filter_blocks; t[1] = r.columns_or_taps; t[2] = r.planes_or_units; t[3] = r.grid;
+    return ok;
+}
+
 // The multiply-high division of the kernels against the plain one: the first n <= nmax whose quotient differs, -1 if
 // none does, -2 if make_fastdiv refuses the pair (it must refuse every pair for which the quotient could be wrong).
 extern "C" long hostmodel_fastdiv_mismatch(long d, long nmax) {

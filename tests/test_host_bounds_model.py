@@ -141,6 +141,22 @@ def test_seeded_random_few_tap_small_dilation(model):
     assert ran >= 450
 
 
+def _split_tile(lib, ps, geom):
+    """(filter blocks, column blocks or taps per wave, planes or units per strip, workgroups) of the FP32 kernels in
+    three bfloat16 parts; None where they do not take the pass."""
+    t = (ctypes.c_long * 4)()
+    return tuple(t) if lib.hostmodel_split_tile(ps, *geom, t) else None
+
+
+def test_small_launches_of_the_three_part_kernels_take_small_tiles(model):
+    """A launch that leaves CUs idle takes narrow tiles (a workgroup alone on its CU takes as long as its chain of steps),
+    one that fills the chip several times takes wide ones."""
+    for C, K, S, d in [(64, 64, 33, 4), (64, 64, 5, 1), (128, 128, 3, 2), (24, 40, 7, 3)]:
+        small = _split_tile(model, 0, (1, C, K, 1000, S, d, (S - 1) * d // 2))
+        large = _split_tile(model, 0, (16, C, K, 30000, S, d, (S - 1) * d // 2))
+        assert small[:2] == (1, 1) and large[0] * large[1] >= 8, (C, K, S, d, small, large)
+
+
 def test_the_model_finds_a_planted_off_by_one():
     """The one GPU memory fault in this library's history: the streamed-weight kernel asked for a stage behind its
     counters and took its sample index one past the batch.  With that repair removed from the model's copy of the
