@@ -764,23 +764,8 @@ hipError_t smallc_wgrad_reduce_launch(const float* ws, float* dw, int K, int C, 
 
 hipError_t smallc_corr_launch_impl(const CorrProblem& p, bool blocks, hipStream_t st);
 
-// One block of channels: the three-part kernels multiply 32 (channel, tap) pairs at a time, 96 cycles per 16 x 16 tile,
-// where the FP32 instruction takes 32 cycles for 4 channels of a tap; their LDS reads cost about half as much again.
-// Below 256 tiles of 256 columns a CU has a single workgroup, which hides none of its staging (C = K = 15, S = 51, d = 8,
-// 60000 columns: 25 us with the FP32 instruction, 28 us with three parts; 960000 columns: 257 and 169 us; C = K = 16,
-// S = 9, 80000 columns: 14.1 and 9.8 us).
-static bool split_is_faster(const CorrProblem& p) {
-    const long fp32 = 32L * cdiv(p.R, 4) * p.S, parts = 96L * cdiv(static_cast<long>(cdiv(p.R, 8)) * p.S, 4);
-    return 2 * fp32 > 3 * parts && static_cast<long>(p.N) * p.Wout > 256 * 256 && split_f32_corr_supported(p);
-}
-// Weight gradients: faster from 200000 columns times taps on (C = K = 15, S = 51, d = 8: 8000 columns 21.8 and 9.2 us,
-// 960000 columns 268 and 182 us; C = K = 4, S = 5, 960000 columns 61 and 35 us); smaller ones are launch and latency.
-static bool split_is_faster(const WgradProblem& p) {
-    return static_cast<long>(p.N) * p.Q * p.S >= 200000 && split_f32_wgrad_supported(p);
-}
-
-bool smallc_corr_is_split(const CorrProblem& p) { return !p.bf16 && split_is_faster(p); }
-bool smallc_wgrad_is_split(const WgradProblem& p) { return !p.bf16 && split_is_faster(p); }
+bool smallc_corr_is_split(const CorrProblem& p) { return split_f32_corr_supported(p); }
+bool smallc_wgrad_is_split(const WgradProblem& p) { return split_f32_wgrad_supported(p); }
 
 bool smallc_corr_supported(const CorrProblem& p) {
     if (p.bf16) return smallc_bf16_corr_supported(p);
@@ -794,7 +779,7 @@ hipError_t smallc_corr_f32_blocks_launch(const CorrProblem& p, hipStream_t st) {
 
 hipError_t smallc_corr_launch(const CorrProblem& p, hipStream_t st) {
     if (p.bf16) return smallc_bf16_corr_launch(p, st);
-    if (split_is_faster(p)) return split_f32_corr_launch(p, st);
+    if (split_f32_corr_supported(p)) return split_f32_corr_launch(p, st);
     return smallc_corr_launch_impl(p, false, st);
 }
 
@@ -834,7 +819,7 @@ hipError_t smallc_wgrad_f32_blocks_launch(const WgradProblem& p, hipStream_t st)
 
 hipError_t smallc_wgrad_launch(const WgradProblem& p, hipStream_t st) {
     if (p.bf16) return smallc_bf16_wgrad_launch(p, st);
-    if (split_is_faster(p)) return split_f32_wgrad_launch(p, st);
+    if (split_f32_wgrad_supported(p)) return split_f32_wgrad_launch(p, st);
     return smallc_wgrad_launch_impl(p, false, st);
 }
 

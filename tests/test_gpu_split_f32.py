@@ -129,8 +129,9 @@ def test_largest_and_smallest_floats(binding):
     assert float((binding.conv1d_fwd(x, w, 1, 0).double() - x.double()).abs().max()) < 2.0 ** -133
 
 
-# layers of more than 16 channels or filters
-BATCH = [(64, 64, 4000, 5, 2), (100, 100, 1000, 9, 1), (40, 24, 1300, 7, 3), (17, 33, 2000, 15, 4)]
+# layers of more than 16 channels or filters, of up to 16, of one kind on either side
+BATCH = [(64, 64, 4000, 5, 2), (100, 100, 1000, 9, 1), (40, 24, 1300, 7, 3), (17, 33, 2000, 15, 4), (15, 15, 5000, 51, 8), (8, 8, 3001, 9, 2),
+         (4, 12, 2500, 25, 1), (64, 16, 4000, 5, 1), (8, 40, 3000, 15, 2)]
 
 
 @pytest.mark.parametrize("case", BATCH, ids=lambda c: "x".join(map(str, c)))
