@@ -53,11 +53,10 @@ bool fp32_pairs_in_one_launch(const WgradProblem& p) {
     return bytes > 0 && bytes <= kMaxPairsWorkspace;
 }
 
-// How a layer with more than one block runs.
+// How a layer with more than one block runs, FP32 layers where the three-part kernels do not take it.
 enum class CorrRoute {
     kNone,
     kRing, kStream, kStaged,   // bf16: one launch of a many-channel kernel
-    kF32Split,                 // fp32: one launch on the bf16 matrix instructions
     kF32Whole,                 // fp32: one launch, channel blocks reduced in the accumulators
     kF32PerChannelBlock,       // fp32: one launch per channel block, accumulating into the output
     kRows,                     // one launch per filter block (each reduces its channel blocks itself)
@@ -75,7 +74,6 @@ CorrRoute corr_route(const CorrProblem& p) {
     if (p.bf16 && igemm_bf16_corr_supported(p)) return CorrRoute::kStaged;
     if (p.R <= kBlock && p.M <= kBlock) return CorrRoute::kNone;  // one block: that is the small-channel family itself
     if (!smallc_corr_supported(corr_block(p, 0, 0))) return CorrRoute::kNone;  // the first block pair is the largest one
-    if (split_f32_corr_supported(p)) return CorrRoute::kF32Split;
     if (!p.bf16) {
         CorrProblem whole = p;
         whole.w_contig = 0;
@@ -103,16 +101,20 @@ bool igemm_corr_supported(const CorrProblem& p) {
     return !(p.epi.out_bf16 && accumulates(r));
 }
 
-bool igemm_corr_is_split(const CorrProblem& p) { return corr_route(p) == CorrRoute::kF32Split; }
+bool igemm_corr_is_split(const CorrProblem& p) { return igemm_corr_supported(p) && split_f32_corr_supported(p); }
 
 hipError_t igemm_corr_launch(const CorrProblem& p, hipStream_t st) {
     if (!igemm_corr_supported(p)) return hipErrorInvalidValue;
+    if (!p.bf16) {
+        bool taken;
+        const hipError_t e = split_f32_corr_launch(p, st, &taken);
+        if (taken) return e;
+    }
     const CorrRoute route = corr_route(p);
     switch (route) {
         case CorrRoute::kRing: return igemm_ring_bf16_corr_launch(p, st);
         case CorrRoute::kStream: return igemm_stream_bf16_corr_launch(p, st);
         case CorrRoute::kStaged: return igemm_bf16_corr_launch(p, st);
-        case CorrRoute::kF32Split: return split_f32_corr_launch(p, st);
         case CorrRoute::kF32Whole: {
             // every filter block in one launch: the kernel holds the weights of all channel blocks of a block
             CorrProblem whole = p;
@@ -189,7 +191,11 @@ hipError_t igemm_wgrad_launch(const WgradProblem& p, hipStream_t st) {
     if (prefer_shift_wgrad(p)) return shift_bf16_wgrad_launch(p, st);
     if (p.bf16 && toeplitz_bf16_wgrad_supported(p)) return toeplitz_bf16_wgrad_launch(p, st);
     if (p.bf16 && blocked_bf16_wgrad_supported(p)) return blocked_bf16_wgrad_launch(p, st);
-    if (fp32_pairs_in_one_launch(p)) return split_f32_wgrad_supported(p) ? split_f32_wgrad_launch(p, st) : smallc_wgrad_f32_blocks_launch(p, st);
+    if (fp32_pairs_in_one_launch(p)) {
+        bool taken;
+        const hipError_t e = split_f32_wgrad_launch(p, st, &taken);
+        return taken ? e : smallc_wgrad_f32_blocks_launch(p, st);
+    }
     for (int k0 = 0; k0 < p.K; k0 += kBlock) {
         for (int c0 = 0; c0 < p.C; c0 += kBlock) {
             const WgradProblem b = wgrad_block(p, k0, c0);

@@ -147,8 +147,10 @@ bool igemm_stream_bf16_corr_supported(const CorrProblem& p);
 hipError_t igemm_stream_bf16_corr_launch(const CorrProblem& p, hipStream_t st);
 
 // FP32 forward / backward-data on the bf16 matrix instructions: every float as the sum of three bfloat16 numbers
+// The launches search a tile, 0.5 to 1 us of host time: they say themselves whether they take the problem (*taken; nothing is
+// launched otherwise), and _supported, which makes the same search, is for queries.
 bool split_f32_corr_supported(const CorrProblem& p);
-hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st);
+hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st, bool* taken);
 // what such a launch would take (the tests choose their geometries by it): filter blocks of 16 per workgroup; column blocks
 // of 64 per workgroup, or taps per wave; planes of 8 channels per step, or units of the longest strip; workgroups
 struct SplitTile {
@@ -159,7 +161,7 @@ bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t);
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
 // FP32 backward-weight the same way; workspace and second stage of smallc_wgrad_f32_blocks_*
 bool split_f32_wgrad_supported(const WgradProblem& p);
-hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st);
+hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken);
 
 // channel-blocked MFMA family
 bool igemm_corr_supported(const CorrProblem& p);

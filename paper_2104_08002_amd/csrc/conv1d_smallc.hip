@@ -779,7 +779,9 @@ hipError_t smallc_corr_f32_blocks_launch(const CorrProblem& p, hipStream_t st) {
 
 hipError_t smallc_corr_launch(const CorrProblem& p, hipStream_t st) {
     if (p.bf16) return smallc_bf16_corr_launch(p, st);
-    if (split_f32_corr_supported(p)) return split_f32_corr_launch(p, st);
+    bool taken;
+    const hipError_t e = split_f32_corr_launch(p, st, &taken);
+    if (taken) return e;
     return smallc_corr_launch_impl(p, false, st);
 }
 
@@ -819,7 +821,9 @@ hipError_t smallc_wgrad_f32_blocks_launch(const WgradProblem& p, hipStream_t st)
 
 hipError_t smallc_wgrad_launch(const WgradProblem& p, hipStream_t st) {
     if (p.bf16) return smallc_bf16_wgrad_launch(p, st);
-    if (split_f32_wgrad_supported(p)) return split_f32_wgrad_launch(p, st);
+    bool taken;
+    const hipError_t e = split_f32_wgrad_launch(p, st, &taken);
+    if (taken) return e;
     return smallc_wgrad_launch_impl(p, false, st);
 }
 

@@ -336,9 +336,10 @@ bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t) {
     return pl.ok;
 }
 
-hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st) {
+hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st, bool* taken) {
     const Plan pl = make_plan(p);
-    if (!pl.ok) return hipErrorInvalidValue;
+    *taken = pl.ok;
+    if (!pl.ok) return hipSuccess;
     return run_tile(pl, st, std::make_index_sequence<sizeof(kTiles) / sizeof(kTiles[0])>{});
 }
 

@@ -281,48 +281,65 @@ Plan make_plan(const WgradProblem& p) {
     const int cblocks = cdiv(p.C, 16), kblocks = cdiv(p.K, 16);
     const long most = static_cast<long>(wsb / (static_cast<size_t>(cblocks) * kblocks * p.S * 1024));
     double best_cost = 0;
+    constexpr int kUnitSizes = 5;  // units of 32 << i positions
+    struct {
+        int upr;
+        long nunits, strips;
+        double longest;  // units of the longest strip
+    } cut[kUnitSizes];
+    for (int i = 0; i < kUnitSizes; ++i) {
+        auto& c = cut[i];
+        c.upr = cdiv(p.Q, 32 << i);
+        c.nunits = static_cast<long>(p.N) * c.upr;
+        c.strips = most < c.nunits ? most : c.nunits;
+        c.longest = c.strips < 1 ? 0.0 : static_cast<double>((c.nunits + c.strips - 1) / c.strips);
+    }
     for (const auto& sh : kShapes) {
         const int fbw = sh[0], ntw = sh[1];
         const int kgroups = cdiv(kblocks, fbw);
         for (int tw_sh = 0; tw_sh <= 3; ++tw_sh) {
             const int taps = ntw << tw_sh, tgroups = cdiv(p.S, taps), WK = 8 >> tw_sh;
-            for (int qc_sh = 5; qc_sh <= 9; ++qc_sh) {
-                const int QC = 1 << qc_sh;
-                if (QC / 32 % WK != 0) continue;
+            const long per_strip = static_cast<long>(cblocks) * kgroups * tgroups;
+            for (int i = 3 - tw_sh; i < kUnitSizes; ++i) {  // a k-step at least for every wave of a tap
+                const int qc_sh = 5 + i, QC = 1 << qc_sh;
+                const auto& c = cut[i];
                 const long lx = QC + static_cast<long>(taps - 1) * p.d;
                 const long ndy = static_cast<long>(fbw) * QC * 2;
                 const size_t stage = static_cast<size_t>(3 * (ndy + 2 * lx)) * 16;
                 const size_t red = WK > 1 ? static_cast<size_t>(taps) * fbw * 1024 : 0;
                 const size_t lds = red > 2 * stage ? red : 2 * stage;
                 if (ndy > kDyTasks * kThreads || 2 * lx > kXTasks * kThreads || lds > kLdsAll) continue;
-                const int upr = cdiv(p.Q, QC);
-                const long nunits = static_cast<long>(p.N) * upr;
-                if (nunits > 0x3fffffffL) continue;
-                long strips = most < nunits ? most : nunits;
-                const long per_strip = static_cast<long>(cblocks) * kgroups * tgroups;
-                if (strips < 1 || strips * per_strip > (1 << 20)) continue;
+                if (c.nunits > 0x3fffffffL || c.strips < 1 || c.strips * per_strip > (1 << 20)) continue;
                 // cycles of a unit on one SIMD's two waves: matrix instructions, LDS reads of all eight, splitting
-                const double steps = QC / 32.0 / WK;
+                const double steps = QC / 32 >> (3 - tw_sh);
                 const double mm = 2 * steps * ntw * fbw * 96;
                 const double rd = 8 * steps * (3.0 * fbw + 3.0 * ntw) * 8;
                 const double staging = 1500 + (cdiv(ndy, kThreads) + cdiv(2 * lx, kThreads)) * 2 * 300.0;
                 const double unit = (mm > rd ? mm : rd) + 0.5 * staging;
-                const double waves = static_cast<double>((strips * per_strip + 255) / 256);
-                const double cost = waves * (unit * static_cast<double>((nunits + strips - 1) / strips) + 10000 + WK * taps * fbw * 16.0);
+                const double waves = static_cast<double>((c.strips * per_strip + 255) / 256);
+                const double cost = waves * (unit * c.longest + 10000 + WK * taps * fbw * 16.0);
                 if (best.ok && cost >= best_cost) continue;
                 best_cost = cost;
                 best.ok = true;
                 best.fbw = fbw;
                 best.ntw = ntw;
                 best.lds = lds;
-                best.grid = static_cast<int>(strips * per_strip);
-                best.a = SwfArgs{static_cast<const float*>(p.x), static_cast<const float*>(p.dy), static_cast<float*>(p.ws), p.C, p.K, p.W, p.Q,
-                                 p.S, p.d, p.P, p.x_sn, p.dy_sn, qc_sh, upr, static_cast<int>(nunits), static_cast<int>(strips), tw_sh, tgroups,
-                                 kgroups, cblocks, static_cast<int>(lx),
-                                 p.Q % 4 == 0 && p.dy_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.dy) & 15) == 0};
+                best.grid = static_cast<int>(c.strips * per_strip);
+                SwfArgs& a = best.a;
+                a.qc_sh = qc_sh; a.upr = c.upr; a.nunits = static_cast<int>(c.nunits); a.strips = static_cast<int>(c.strips);
+                a.tw_sh = tw_sh; a.tgroups = tgroups; a.kgroups = kgroups; a.lx = static_cast<int>(lx);
             }
         }
     }
+    if (!best.ok) return best;
+    SwfArgs& a = best.a;
+    a.x = static_cast<const float*>(p.x);
+    a.dy = static_cast<const float*>(p.dy);
+    a.ws = static_cast<float*>(p.ws);
+    a.C = p.C; a.K = p.K; a.W = p.W; a.Q = p.Q; a.S = p.S; a.d = p.d; a.P = p.P;
+    a.x_sn = p.x_sn; a.dy_sn = p.dy_sn;
+    a.cblocks = cblocks;
+    a.vec = p.Q % 4 == 0 && p.dy_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.dy) & 15) == 0;
     return best;
 }
 
@@ -344,9 +361,10 @@ bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
     return pl.ok;
 }
 
-hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st) {
+hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken) {
     const Plan pl = make_plan(p);
-    if (!pl.ok) return hipErrorInvalidValue;
+    *taken = pl.ok;
+    if (!pl.ok) return hipSuccess;
     hipError_t e;
     switch (pl.fbw * 16 + pl.ntw) {
         case 16 + 3: e = run<1, 3>(pl, st); break;
