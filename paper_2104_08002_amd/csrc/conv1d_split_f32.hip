@@ -241,6 +241,8 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
     f.wlen = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
     f.lds = (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16;
     if (f.wlen > 16384 || f.lds > kLdsAll) return f;
+    const long columns = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * 64 * t.pb;  // the last tile may end behind the row
+    if (columns > 1L << 31 || columns - 64 * t.pb - p.P + f.wlen > 1L << 31) return f;  // 32-bit columns in the kernel
     const int by_lds = static_cast<int>(kLdsAll / f.lds), by_regs = 512 / (94 + 12 * t.fbw + 4 * t.fbw * t.pb);
     f.resident = by_lds < by_regs ? by_lds : by_regs;
     if (f.resident < 1) f.resident = 1;

@@ -157,6 +157,24 @@ def test_small_launches_of_the_three_part_kernels_take_small_tiles(model):
         assert small[:2] == (1, 1) and large[0] * large[1] >= 8, (C, K, S, d, small, large)
 
 
+def test_columns_of_the_three_part_kernels_stay_within_32_bits(model):
+    """An output row may be up to 2^31 - 1 columns wide: no tile may end behind the last number a 32-bit column can take
+    (its last columns would come out negative and pass for columns of the row)."""
+    for short in (0, 1, 63, 130, 200, 300, 700):
+        Q = 2 ** 31 - 1 - short
+        for C, K, S, d in [(32, 17, 1, 1), (32, 64, 2, 1), (16, 40, 3, 5), (40, 50, 5, 2)]:
+            W = 2000 + (1 - (Q + (S - 1) * d) % 2)
+            P = (Q - W + (S - 1) * d) // 2
+            if W + 2 * P - (S - 1) * d != Q:
+                W += 1
+                P = (Q - W + (S - 1) * d) // 2
+            assert W + 2 * P - (S - 1) * d == Q
+            t = _split_tile(model, 0, (1, C, K, W, S, d, P))
+            if t:
+                width = 64 * t[1]
+                assert (Q + width - 1) // width * width <= 2 ** 31, (Q, C, K, S, d, t)
+
+
 def test_the_model_finds_a_planted_off_by_one():
     """The one GPU memory fault in this library's history: the streamed-weight kernel asked for a stage behind its
     counters and took its sample index one past the batch.  With that repair removed from the model's copy of the
