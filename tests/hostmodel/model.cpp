@@ -64,9 +64,12 @@ void on_fault(int, siginfo_t* info, void*) {
 }
 }  // namespace
 
+int g_launches = 0;  // kernel launches of the last hostmodel_run
+
 void* dynamic_lds() { return g_lds.data; }
 
 void run_grid(dim3 grid, dim3 block, size_t lds_bytes, const std::function<void()>& fn) {
+    ++g_launches;
     free_region(g_lds);
     g_lds = make_region(lds_bytes, true, "dynamic LDS");
     g_grid = Idx{grid.x, grid.y, grid.z};
@@ -127,6 +130,7 @@ extern "C" int hostmodel_run(int pass, int N, int C, int K, int W, int S, int d,
     sigaction(SIGSEGV, &sa, &old_segv);
     sigaction(SIGBUS, &sa, &old_bus);
     conv1d_set_variant(variant);
+    g_launches = 0;
     int rc;
     if (sigsetjmp(g_jump, 1) == 0) {
         g_armed = 1;
@@ -171,6 +175,8 @@ extern "C" int hostmodel_run(int pass, int N, int C, int K, int W, int S, int d,
 extern "C" const char* hostmodel_kernel_name(int pass, int N, int C, int K, int W, int S, int d, int P, int dtype) {
     return conv1d_kernel_name(pass, N, C, K, W, S, d, P, dtype);
 }
+
+extern "C" int hostmodel_launches() { return g_launches; }
 
 // Tile of the FP32 kernels in three bfloat16 parts for a pass (0 forward, 1 backward-data, 2 backward-weight): t[0 .. 3] as
 // conv1d::SplitTile; returns 0 where the pass cannot run on them.

@@ -39,10 +39,14 @@ CASES = [
     ("epi_ring_k40",     2, 72,  40,  1000, 7,  4,  12),
     ("epi_stream",       4, 200, 1056, 1100, 9, 4,  16),  # streamed weights
     ("epi_staged_d3",    2, 40,  24,  2500, 9,  3,  12),  # staged many-channel kernel
-    ("epi_c64_S9",       2, 64,  64,  1100, 9,  1,  4),   # fp32: one launch, channel blocks in the accumulators
-    ("epi_c64_S51",      1, 64,  64,  1536, 51, 8,  200), # fp32: one launch per channel block, epilogue kernel at the end
-    ("epi_pairs_oddW",   2, 40,  24,  901,  7,  3,  9),   # odd width: 16 x 16 block launches
+    ("epi_c64_S9",       2, 64,  64,  1100, 9,  1,  4),   # fp32: three bfloat16 parts
+    ("epi_c64_S51",      1, 64,  64,  1536, 51, 8,  200), # fp32: three bfloat16 parts, long windows
+    ("epi_pairs_oddW",   2, 40,  24,  901,  7,  3,  9),   # odd width: element-wise stores
     ("epi_tiny",         2, 4,   4,   256,  5,  2,  0),
+    # fp32 layers the three-part kernels leave (sums of fewer than 32 products; windows too wide for three parts)
+    ("epi_f32_whole",    2, 3,   40,  1100, 5,  3,  6),      # one launch, channel blocks in the accumulators
+    ("epi_f32_wide",     1, 8,   24,  3200, 4,  1100, 100),  # the same, for its window
+    ("epi_f32_blocks",   1, 92,  20,  2320, 2,  2101, 0),    # one launch per channel block, epilogue kernel at the end
 ]
 EPILOGUES = [
     # bias, relu, out_bf16

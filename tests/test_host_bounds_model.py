@@ -148,6 +148,43 @@ def _split_tile(lib, ps, geom):
     return tuple(t) if lib.hostmodel_split_tile(ps, *geom, t) else None
 
 
+def test_three_part_tiles_of_the_parity_cases(model):
+    """The geometries of the GPU parity suite land on the tiles it says, every tile the library has is among them, and no
+    access of these launches leaves its tensor."""
+    sys.path.insert(0, HERE)
+    import test_gpu_split_f32 as t
+
+    seen = set()
+    for i, (what, tile, geom) in enumerate(t.TILES):
+        ps = t.PASSES.index(what)
+        assert _split_tile(model, ps, geom)[:3] == tile, (what, tile, geom)
+        seen.add((ps == 2,) + tile[:2])
+        _check(model, geom, 0, passes=(ps,), placements=(i % 3,))
+    for geom in t.EDGES:
+        _check(model, geom, 0, passes=(0, 1, 2), placements=(0,))
+    rng = np.random.default_rng(3)
+    for _ in range(3000):
+        geom = tuple(int(v) for v in (rng.integers(1, 65), np.exp(rng.uniform(0, 5.7)), np.exp(rng.uniform(0, 5.7)),
+                                      np.exp(rng.uniform(3, 11)), rng.integers(1, 53), rng.integers(1, 17), 0))
+        if geom[3] > (geom[4] - 1) * geom[5]:
+            for ps in range(3):
+                tile = _split_tile(model, ps, geom)
+                assert tile is None or (ps == 2,) + tile[:2] in seen, (ps, geom, tile)
+
+
+def test_launches_of_fp32_layers_off_the_three_part_kernels(model):
+    """What the three-part kernels leave still runs as before: one launch while the weights of all channel blocks and the
+    window fit in LDS, else one per channel block, with bias and ReLU in a launch of their own at the end."""
+    for geom, fwd, fwd_ex in [((2, 3, 40, 1100, 5, 3, 6), 1, 1), ((1, 8, 24, 3200, 4, 1100, 100), 1, 1), ((1, 92, 20, 2320, 2, 2101, 0), 6, 7)]:
+        assert _split_tile(model, 0, geom) is None
+        for ps, n in ((0, fwd), (4, fwd_ex)):
+            for placement in (0, 1, 2):
+                assert _run(model, ps, geom, 0, 0, placement) == (0, "")
+                assert model.hostmodel_launches() == n, (geom, ps)
+    assert _split_tile(model, 0, (2, 64, 64, 3007, 33, 4, 64)) is not None
+    assert _run(model, 0, (2, 64, 64, 3007, 33, 4, 64), 0) == (0, "") and model.hostmodel_launches() == 1
+
+
 def test_small_launches_of_the_three_part_kernels_take_small_tiles(model):
     """A launch that leaves CUs idle takes narrow tiles (a workgroup alone on its CU takes as long as its chain of steps),
     one that fills the chip several times takes wide ones."""
