@@ -47,18 +47,19 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Shortest sum taken, one matrix instruction deep, and the only rule: what has more terms and fits in LDS runs here, for any
-// number of channels, filters, columns and samples.  (A rule that asked how many samples there are would give a sample
-// other bits in another batch.)
+// Shortest sum taken, and the only rule: what has more terms and fits in LDS runs here, for any number of channels,
+// filters, columns and samples.  (A rule that asked how many samples there are would give a sample other bits in another
+// batch.)
 // Error: the instruction's additions cut off, once per step, where the FP32 instruction rounds to nearest, once per four
-// products.  Norm of the error against 64 bits, FP32 instruction and three parts: normal values 2.5e-8 and 3.6e-8 (1
-// product), 5.6 and 3.1 (8), 10 and 3.8 (32); tracks of 80 % zeros 2.5 and 3.6 (1), 3.3 and 3.4 (8), 5.1 and 3.5 (32).
+// products.  Norm of the error against 64 bits in 1e-8, FP32 instruction and three parts: normal values 2.5 and 3.6 (1
+// product), 5.4 and 3.1 (8), 7.4 and 3.4 (16), 10 and 3.8 (31); tracks of 80 % zeros, whose sums have a fifth of the
+// products, 2.5 and 3.6 (1), 3.3 and 3.4 (8), 4.0 and 3.4 (16), 5.1 and 3.5 (31).
 // Time, forward with S = 51, d = 8 on FP32 instruction and three parts, at 1000, 60000 and 960000 columns: C = K = 15 22.8
 // and 17.7, 24.0 and 23.4, 226 and 134 us; C = K = 12 18.9 and 17.7, 19.9 and 23.1, 178 and 125; C = K = 4 10.6 and 9.8,
 // 11.0 and 12.6, 83 and 63 (four channels are multiplied as eight, twelve as sixteen: slower where one wave of workgroups
 // just fills the chip, faster on either side).  Weight gradient, C = K = 15: 24.4 and 10.0, 31.7 and 26.6, 245 and
 // 144 us.
-constexpr long kMinTerms = 32;
+constexpr long kMinTerms = 16;
 
 // The six products of a step start from zero, smallest first, and their sum is added to the running one in an ordinary
 // FP32 addition.  Chained through the running sums themselves the matrix instruction's additions lost more than the

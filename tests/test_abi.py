@@ -134,10 +134,11 @@ def test_fp32_kernel_names_tell_the_instruction():
     binding.conv1d_set_variant(binding.VARIANT_AUTO)
     assert [name(i, 8, 64, 64, 20000, 33, 4, 64, 0) for i in range(3)] == ["igemm_split_mfma_fp32"] * 2 + ["igemm_wgrad_split_mfma_fp32"]
     assert [name(i, 16, 15, 15, 60000, 51, 8, 200, 0) for i in range(3)] == ["smallc_split_mfma_fp32"] * 2 + ["smallc_wgrad_split_mfma_fp32"]
-    assert [name(i, 2, 4, 4, 256, 5, 2, 0, 0) for i in range(3)] == ["smallc_mfma_fp32"] * 2 + ["smallc_wgrad_split_mfma_fp32"]
-    # a sum of fewer products than one bf16 matrix instruction is deep stays on the FP32 instruction
-    assert [name(0, 4, C, 40, 4000, 1, 1, 0, 0) for C in (31, 32)] == ["igemm_mfma_fp32", "igemm_split_mfma_fp32"]
-    assert [name(2, 1, 40, 40, W, 1, 1, 0, 0) for W in (31, 32)] == ["igemm_wgrad_mfma_fp32", "igemm_wgrad_split_mfma_fp32"]
+    # a sum of fewer than 16 products stays on the FP32 instruction
+    assert [name(i, 2, 3, 3, 256, 5, 2, 0, 0) for i in range(3)] == ["smallc_mfma_fp32"] * 2 + ["smallc_wgrad_split_mfma_fp32"]
+    assert [name(0, 4, C, 40, 4000, 1, 1, 0, 0) for C in (15, 17)] == ["igemm_mfma_fp32", "igemm_split_mfma_fp32"]
+    assert [name(0, 4, 4, 4, 4000, S, 1, 0, 0) for S in (3, 4)] == ["smallc_mfma_fp32", "smallc_split_mfma_fp32"]
+    assert [name(2, 1, 40, 40, W, 1, 1, 0, 0) for W in (15, 16)] == ["igemm_wgrad_mfma_fp32", "igemm_wgrad_split_mfma_fp32"]
     # three parts of a window of 2 x 2485 columns and a tile do not fit in LDS
     assert name(0, 1, 3, 40, 30000, 3, 2485, 2485, 0) == "igemm_mfma_fp32"
 

@@ -43,7 +43,7 @@ CASES = [
     ("epi_c64_S51",      1, 64,  64,  1536, 51, 8,  200), # fp32: three bfloat16 parts, long windows
     ("epi_pairs_oddW",   2, 40,  24,  901,  7,  3,  9),   # odd width: element-wise stores
     ("epi_tiny",         2, 4,   4,   256,  5,  2,  0),
-    # fp32 layers the three-part kernels leave (sums of fewer than 32 products; windows too wide for three parts)
+    # fp32 layers the three-part kernels leave (sums of fewer than 16 products; windows too wide for three parts)
     ("epi_f32_whole",    2, 3,   40,  1100, 5,  3,  6),      # one launch, channel blocks in the accumulators
     ("epi_f32_wide",     1, 8,   24,  3200, 4,  1100, 100),  # the same, for its window
     ("epi_f32_blocks",   1, 92,  20,  2320, 2,  2101, 0),    # one launch per channel block, epilogue kernel at the end
