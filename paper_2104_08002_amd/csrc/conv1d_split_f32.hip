@@ -262,9 +262,10 @@ int planes_shift(const CorrProblem& p) {
     int best = -1;
     double best_cost = 0;
     for (const Tile t : kTiles) {
+        if (t.pb < 4 || 16 * (t.fbw - 1) >= p.M) continue;  // (no more filter blocks than there are: those tiles lose anyway)
         for (int sh = 0; sh <= 2; ++sh) {
             const Fit f = fit(p, t, sh);
-            if (!f.ok || t.pb < 4) continue;
+            if (!f.ok) continue;
             const double beside = f.nsteps * 600.0 + 1000.0 + (f.wlen << sh) * 2.0;
             const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * f.lds <= kLdsAll ? 0.5 : 1.0) * beside);
             if (best >= 0 && cost >= best_cost) continue;
@@ -283,6 +284,7 @@ Plan make_plan(const CorrProblem& p) {
     Fit bf{};
     double best_time = 0;
     for (const Tile t : kTiles) {
+        if (16 * (t.fbw - 1) >= p.M) continue;
         const Fit f = fit(p, t, sh);
         if (!f.ok) continue;
         const long grid = p.N * f.per_sample;

@@ -299,6 +299,7 @@ Plan make_plan(const WgradProblem& p) {
     }
     for (const auto& sh : kShapes) {
         const int fbw = sh[0], ntw = sh[1];
+        if (fbw > 1 && ntw > 2 && fbw / 2 >= kblocks) continue;  // half the filter blocks would do: such a shape loses anyway
         const int kgroups = cdiv(kblocks, fbw);
         for (int tw_sh = 0; tw_sh <= 3; ++tw_sh) {
             const int taps = ntw << tw_sh, tgroups = cdiv(p.S, taps), WK = 8 >> tw_sh;
