@@ -55,7 +55,9 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
     constexpr int NG = 4 / FBW;
     const bool has_entry = wave < NG * FBW;
     const int ef = wave % FBW, em = m0 + ef * 16 + l16;  // filter of this thread's entry; lane group g has plane and tap
-    const float* wrow = a.wt + min(em, a.M - 1) * a.w_sm + a.w_s0;
+    // byte offsets in the weights, which the plan keeps below 2^32
+    const unsigned wrow = 4u * static_cast<unsigned>(min(em, a.M - 1) * a.w_sm + a.w_s0);
+    const unsigned wchan = 4u * static_cast<unsigned>(a.w_sr), wlast = static_cast<unsigned>(a.R - 1) * wchan;
     const int eplane = g & (PL - 1), etap = g >> a.pl_sh;
     const int total = a.nstages * a.nsteps;
     int due = wave / FBW;  // step, counted over all stages, of the entry in wv
@@ -69,10 +71,12 @@ __global__ __launch_bounds__(kThreads, 2) void split_corr_f32_kernel(SpArgs a) {
             ++wstage;
         }
         const int tap = wstep * TP + etap, c = 8 * (wstage * PL + eplane);
-        const float* p = wrow + static_cast<long>(min(tap, a.S - 1)) * a.w_ss;
+        const unsigned row = wrow + 4u * static_cast<unsigned>(min(tap, a.S - 1) * a.w_ss);
         cleft = (em < a.M && tap < a.S) ? a.R - c : 0;
+        unsigned at = static_cast<unsigned>(c) * wchan;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) wv[j] = p[min(c + j, a.R - 1) * a.w_sr];
+        for (int j = 0; j < 8; ++j, at += wchan)
+            wv[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.wt) + (row + min(at, wlast)));
     };
     // entry of the given step, if this wave has it.  Channels, taps and filters the layer does not have count as zero; put
     // right here, so that nothing waits for the loads before the products of a step are done
@@ -279,6 +283,7 @@ int planes_shift(const CorrProblem& p) {
 Plan make_plan(const CorrProblem& p) {
     Plan best{};
     if (p.bf16 || p.accumulate || p.epi.out_bf16 || p.tail.ws || static_cast<long>(p.R) * p.S < kMinTerms) return best;
+    if (static_cast<long>(p.M) * p.R * p.S >= 1L << 30) return best;  // 32-bit byte offsets in the weights
     const int sh = planes_shift(p);
     if (sh < 0) return best;
     Fit bf{};

@@ -194,6 +194,13 @@ def test_small_launches_of_the_three_part_kernels_take_small_tiles(model):
         assert small[:2] == (1, 1) and large[0] * large[1] >= 8, (C, K, S, d, small, large)
 
 
+def test_weights_of_the_three_part_kernels_stay_within_32_bits(model):
+    """Weights are read at 32-bit byte offsets: a layer of 2^30 weights and more is left to the other kernels."""
+    for C, K, S, taken in [(8192, 8192, 15, True), (8192, 8192, 16, False), (4096, 8191, 32, True), (4096, 8192, 32, False)]:
+        for ps in (0, 1):
+            assert (_split_tile(model, ps, (1, C, K, 500, S, 1, 0)) is not None) == taken, (C, K, S, ps)
+
+
 def test_columns_of_the_three_part_kernels_stay_within_32_bits(model):
     """An output row may be up to 2^31 - 1 columns wide: no tile may end behind the last number a 32-bit column can take
     (its last columns would come out negative and pass for columns of the row)."""
