@@ -239,6 +239,36 @@ def test_cut_off_of_weight_gradients_cancels(binding, case):
     assert norm <= 2.2e-7 and mean <= 1e-7, (norm, mean)
 
 
+# layers of 6 and 10, of 10 and 26 steps
+EVEN_STEPS = [(24, 40, 7, 3), (64, 64, 5, 1), (40, 24, 7, 3), (15, 15, 51, 8)]
+
+
+@pytest.mark.parametrize("case", EVEN_STEPS, ids=lambda c: "x".join(map(str, c)))
+def test_cut_off_of_forward_and_backward_data_cancels(binding, case):
+    """Every step's sum is cut off towards minus infinity; steps alternate in sign, so the mean error of a million outputs
+    is that of a million independent roundings, 1e-7 / 1000 of their size (-1.6e-8 with all steps added)."""
+    import torch
+
+    C, K, S, d = case
+    N, W, P = 6, 5000, (S - 1) * d // 2
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    x = torch.randn((N, C, W), generator=gen, device="cuda")
+    dy = torch.randn((N, K, W + 2 * P - (S - 1) * d), generator=gen, device="cuda")
+    w = torch.randn((K, C, S), generator=gen, device="cuda")
+
+    def exact(t, wt, pad):
+        tp = torch.nn.functional.pad(t.double(), (pad, pad))
+        n = tp.shape[2] - (S - 1) * d
+        return sum(torch.matmul(wt[:, :, s].double().contiguous(), tp[:, :, s * d:s * d + n].contiguous()) for s in range(S))
+
+    pairs = {"fwd": (binding.conv1d_fwd(x, w, d, P), exact(x, w, P)),
+             "bwd_data": (binding.conv1d_bwd_data(dy, w, W, d, P), exact(dy, w.transpose(0, 1).flip(2), (S - 1) * d - P))}
+    for what, (got, ref) in pairs.items():
+        mean = float((got.double() - ref).mean() / ref.square().mean().sqrt())
+        print(case, what, mean, flush=True)
+        assert abs(mean) <= 2e-9, (what, mean)
+
+
 def test_largest_and_smallest_floats(binding):
     """One weight of 1 per filter: the output is the input, up to the largest float (no part overflows) and down to
     2^-110; below that the parts lose what lies under 2^-133."""
