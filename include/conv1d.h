@@ -59,14 +59,26 @@
  *   Every other output is computed as if the input were finite, and every
  *   output that the definition makes non-finite is non-finite.
  *
+ * FP32 arithmetic
+ *   Sums of at least 16 products (C*S in conv1d_fwd, K*S in conv1d_bwd_data,
+ *   N*Q in conv1d_bwd_weight) are multiplied on the bf16 matrix instructions:
+ *   every float is the sum of three bfloat16 numbers and a product the six
+ *   largest of their nine products, at most 2^-24 of it left out.  Measured
+ *   against 64 bits the results are at least as close as sums of FP32 products.
+ *   A value is carried to 2^-133, so one below 2^-110 has fewer than 24 bits;
+ *   an infinite input makes the outputs it contributes to NaN.  Shorter sums,
+ *   and layers whose window does not fit in LDS so, use FP32 products.
+ *   FP32 results of conv1d_fwd and conv1d_bwd_data for a sample have the same
+ *   bits whatever other samples the call has.
+ *
  * Errors
  *   Every int-returning entry point returns CONV1D_OK (0) or a negative
  *   conv1d_status_t; nothing is thrown and errno is untouched.  Argument errors
  *   (CONV1D_EINVAL, CONV1D_EUNSUPPORTED, CONV1D_EWORKSPACE) are detected before
  *   anything is launched.  CONV1D_EHIP reports that the HIP runtime refused a
  *   launch; a pass that consists of several launches (FP32 layers with more
- *   than 16 channels whose weights do not fit in LDS; the second stage of
- *   conv1d_bwd_weight) may have enqueued its earlier kernels by then, so the
+ *   than 16 channels whose window or weights do not fit in LDS; the second
+ *   stage of conv1d_bwd_weight) may have enqueued its earlier kernels by then, so the
  *   output is unspecified after CONV1D_EHIP.
  */
 #ifndef CONV1D_MI355X_H

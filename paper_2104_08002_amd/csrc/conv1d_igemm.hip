@@ -9,6 +9,7 @@
 //                   its accumulators), else one launch per pair: the first channel block overwrites the output,
 //                   the following ones accumulate
 //   bwd_weight      dw[kb, cb, :]  = wgrad(x[:, cb, :], dy[:, kb, :])      each pair owns its block of dw
+// FP32 layers run like this only where the kernels on three bfloat16 parts (conv1d_split_f32.hip) do not take them.
 // All launches go to the caller's stream in a fixed order, so results are deterministic and the one
 // workspace is reused by every pair.
 #include "conv1d_internal.h"

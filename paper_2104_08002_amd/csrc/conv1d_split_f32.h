@@ -54,11 +54,11 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
 // products.  Norm of the error against 64 bits in 1e-8, FP32 instruction and three parts: normal values 2.5 and 3.6 (1
 // product), 5.4 and 3.1 (8), 7.4 and 3.4 (16), 10 and 3.8 (31); tracks of 80 % zeros, whose sums have a fifth of the
 // products, 2.5 and 3.6 (1), 3.3 and 3.4 (8), 4.0 and 3.4 (16), 5.1 and 3.5 (31).
-// Time, forward with S = 51, d = 8 on FP32 instruction and three parts, at 1000, 60000 and 960000 columns: C = K = 15 22.8
-// and 17.7, 24.0 and 23.4, 226 and 134 us; C = K = 12 18.9 and 17.7, 19.9 and 23.1, 178 and 125; C = K = 4 10.6 and 9.8,
-// 11.0 and 12.6, 83 and 63 (four channels are multiplied as eight, twelve as sixteen: slower where one wave of workgroups
-// just fills the chip, faster on either side).  Weight gradient, C = K = 15: 24.4 and 10.0, 31.7 and 26.6, 245 and
-// 144 us.
+// Time, forward with S = 51, d = 8 on FP32 instruction and three parts, at 1000, 60000 and 960000 columns: C = K = 15 22.9
+// and 16.2, 24.0 and 22.1, 226 and 130 us; C = K = 12 18.9 and 16.1, 20.0 and 21.9, 177 and 123; C = K = 4 10.6 and 9.0,
+// 10.9 and 12.1, 83 and 63 (four channels are multiplied as eight, twelve as sixteen: slower where one wave of workgroups
+// just fills the chip, faster on either side).  Weight gradient, C = K = 15: 24.3 and 10.1, 31.7 and 26.8, 246 and
+// 145 us.
 constexpr long kMinTerms = 16;
 
 // The six products of a step start from zero, smallest first, and their sum is added to the running one in an ordinary

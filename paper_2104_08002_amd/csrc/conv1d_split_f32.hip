@@ -6,6 +6,8 @@
 // products left out are at most 2^-24 of the whole, half a unit in the last place of an FP32 product.  The sum of the six
 // over 32 terms is added to the running sums in FP32, so a sum of n terms is rounded n/32 times at full size where the
 // FP32 instruction rounded it n/4 times.
+// One pass, N = 8, C = K = 64, W = 20000, FP32 instruction and three parts: S = 5, d = 1 116 and 52 us, S = 33, d = 4 447 and
+// 222 us, S = 51, d = 8 658 and 297 us (225 TFLOP/s, 54 % of the rate of six bf16 products).
 //
 // One workgroup: 16 FBW filters x 64 PB output columns of one sample, wave v the columns 16 PB v ..  A step is one
 // matrix instruction deep (32 = 4 lane groups x 8 channels): PL planes of 8 channels times 4/PL taps.  The input

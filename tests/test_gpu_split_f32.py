@@ -288,9 +288,9 @@ def test_largest_and_smallest_floats(binding):
     assert float((binding.conv1d_fwd(x, w, 1, 0).double() - x.double()).abs().max()) < 2.0 ** -133
 
 
-# layers of more than 16 channels or filters, of up to 16, of one kind on either side
+# layers of more than 16 channels or filters, of up to 16, of one kind on either side, on the FP32 instruction
 BATCH = [(64, 64, 4000, 5, 2), (100, 100, 1000, 9, 1), (40, 24, 1300, 7, 3), (17, 33, 2000, 15, 4), (15, 15, 5000, 51, 8), (8, 8, 3001, 9, 2),
-         (4, 12, 2500, 25, 1), (64, 16, 4000, 5, 1), (8, 40, 3000, 15, 2)]
+         (4, 12, 2500, 25, 1), (64, 16, 4000, 5, 1), (8, 40, 3000, 15, 2), (3, 40, 3000, 5, 3), (3, 2, 5000, 5, 8)]
 
 
 @pytest.mark.parametrize("case", BATCH, ids=lambda c: "x".join(map(str, c)))
@@ -299,7 +299,7 @@ def test_a_sample_does_not_depend_on_its_batch(binding, case):
     launch, the order of the sums must not."""
     import torch
 
-    C, K, W, S, d = case
+    C, K, W, S, d = case  # (the last two: forward sums of 15 products)
     P = (S - 1) * d // 2
     Q = W + 2 * P - (S - 1) * d
     gen = torch.Generator(device="cuda").manual_seed(11)
