@@ -194,6 +194,30 @@ int conv1d_bwd(const void* x, const void* dy, const void* w, float* dx, float* d
                int N, int C, int K, int W, int S, int dilation, int padding,
                int dtype, void* stream);
 
+/* conv1d_bwd whose dx is stored as bfloat16 with CONV1D_EPI_OUT_BF16, as by conv1d_bwd_data_ex (flags = 0: conv1d_bwd).
+ * CONV1D_EUNSUPPORTED when the layer's backward-data kernel has to keep partial sums in a float dx. */
+int conv1d_bwd_ex(const void* x, const void* dy, const void* w, void* dx, float* dw,
+                  void* workspace, size_t workspace_bytes,
+                  int N, int C, int K, int W, int S, int dilation, int padding,
+                  int dtype, int flags, void* stream);
+
+/* Backward of the fused epilogue.  conv1d_relu_mask records where an output y of conv1d_fwd_ex is positive: element i
+ * in bit i % 8 of byte i / 8 of `positive`.
+ * y: device, dtype, count elements (read).  positive: device, (count + 7) / 8 bytes (overwritten). */
+int conv1d_relu_mask(const void* y, void* positive, size_t count, int dtype, void* stream);
+
+/* The gradient gy of such an output, taken through the ReLU and the bias:
+ *   dy[n][k][q] = gy[n][k][q] * (positive ? 1 or 0 : 1), stored as dy_dtype       (not stored when dy is NULL)
+ *   dbias[k]    = sum over n, q of that product in FP32, before it is rounded      (not summed when dbias is NULL)
+ * gy: device, gy_dtype, N*K*Q elements (read).  positive: device, from conv1d_relu_mask, or NULL for no ReLU.
+ * dy: device, dy_dtype, N*K*Q elements, or NULL; bfloat16 where gy is.  dbias: device, float, K elements, or NULL.
+ * workspace: device, 4-byte aligned, at least conv1d_epilogue_bwd_workspace_bytes(N, K, Q) bytes if dbias is wanted.
+ * The order of the sums is fixed. */
+size_t conv1d_epilogue_bwd_workspace_bytes(int N, int K, int Q);
+int conv1d_epilogue_bwd(const void* gy, const void* positive, void* dy, float* dbias,
+                        void* workspace, size_t workspace_bytes,
+                        int N, int K, int Q, int gy_dtype, int dy_dtype, void* stream);
+
 /* conv1d_bwd_weight for callers that cannot allocate device memory or bring a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same result, bit for bit, as conv1d_bwd_weight on the same

@@ -1,7 +1,7 @@
 """The layer as a ``torch.autograd.Function`` and an ``nn.Module`` on top of the C-ABI binding.
 
-Glue only: every arithmetic step of the three passes runs in the library's kernels; torch supplies device memory,
-the stream, the autograd graph and (as in the paper, Section 3) the gradient of the bias.  This is the interface the
+Glue only: every arithmetic step of the three passes and of the bias and ReLU around them runs in the library's kernels;
+torch supplies device memory, the stream and the autograd graph.  This is the interface the
 paper's single-layer measurements use (Section 4.3: ``net.forward(x)`` and ``out.sum().backward()``).
 """
 from __future__ import annotations
@@ -27,20 +27,28 @@ class Conv1dFunction(torch.autograd.Function):
         else:
             y = binding.conv1d_fwd(x, w, dilation, padding)
         ctx.relu = relu
-        if relu:
-            ctx.y_positive = y > 0
+        if relu and any(ctx.needs_input_grad):
+            # not y itself: what follows the layer may change it in place
+            ctx.y_positive = binding.conv1d_relu_mask(y)
         return y
 
     @staticmethod
     def backward(ctx, gy):
         x, w = ctx.saved_tensors
         d, P = ctx.geometry
-        if ctx.relu:
-            gy = gy * ctx.y_positive
-        gb = gy.float().sum(dim=(0, 2)) if ctx.has_bias else None     # the framework's part (Section 3)
-        dy = gy.to(x.dtype).contiguous()                               # no copy when the dtypes already agree
-        dx, dw = binding.conv1d_bwd(x, dy, w, d, P)
-        return dx.to(x.dtype), dw.to(w.dtype), gb, None, None, None, None
+        bf16 = x.dtype == torch.bfloat16
+        if torch.is_grad_enabled() and gy.requires_grad:   # create_graph: the bias gradient is differentiable in gy
+            dy = gy
+            if ctx.relu:
+                bit = torch.arange(8, dtype=torch.uint8, device=gy.device)
+                dy = gy * ((ctx.y_positive[:, None] >> bit) & 1).bool().flatten()[:gy.numel()].view(gy.shape)
+            gb = dy.float().sum(dim=(0, 2)) if ctx.has_bias else None
+            dy = dy.to(x.dtype).contiguous()
+        else:
+            dy, gb = binding.conv1d_epilogue_bwd(gy.resolve_neg().contiguous(), ctx.y_positive if ctx.relu else None, x.dtype,
+                                                 ctx.has_bias)
+        dx, dw = binding.conv1d_bwd_ex(x, dy, w, d, P, out_bf16=bf16)
+        return dx, dw.to(w.dtype), gb, None, None, None, None
 
 
 def conv1d(x, w, bias=None, dilation: int = 1, padding: int = 0, relu: bool = False, bf16_out: bool = False):

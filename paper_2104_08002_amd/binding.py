@@ -16,10 +16,12 @@ LIB_PATH = os.path.join(_HERE, "libconv1d_mi355x.so")
 CONV1D_FP32, CONV1D_BF16 = 0, 1
 VARIANT_AUTO, VARIANT_GENERIC, VARIANT_SMALLC, VARIANT_IGEMM = 0, 1, 2, 3
 PASS_FWD, PASS_BWD_DATA, PASS_BWD_WEIGHT = 0, 1, 2
+STATUS_EUNSUPPORTED = -2
 
 EXPORTS = (
     "conv1d_out_width", "conv1d_fwd", "conv1d_fwd_ex", "conv1d_bwd_data", "conv1d_bwd_data_ex",
     "conv1d_bwd_weight_workspace_bytes", "conv1d_bwd_workspace_bytes", "conv1d_bwd",
+    "conv1d_bwd_ex", "conv1d_relu_mask", "conv1d_epilogue_bwd_workspace_bytes", "conv1d_epilogue_bwd",
     "conv1d_bwd_weight", "conv1d_bwd_weight_noalloc", "conv1d_set_variant", "conv1d_kernel_name", "conv1d_status_string",
 )
 
@@ -63,6 +65,14 @@ def load() -> ctypes.CDLL:
     lib.conv1d_bwd_workspace_bytes.argtypes = geom + [i]
     lib.conv1d_bwd.restype = i
     lib.conv1d_bwd.argtypes = [vp, vp, vp, vp, vp, vp, sz] + geom + [i, vp]
+    lib.conv1d_bwd_ex.restype = i
+    lib.conv1d_bwd_ex.argtypes = [vp, vp, vp, vp, vp, vp, sz] + geom + [i, i, vp]
+    lib.conv1d_relu_mask.restype = i
+    lib.conv1d_relu_mask.argtypes = [vp, vp, sz, i, vp]
+    lib.conv1d_epilogue_bwd_workspace_bytes.restype = sz
+    lib.conv1d_epilogue_bwd_workspace_bytes.argtypes = [i] * 3
+    lib.conv1d_epilogue_bwd.restype = i
+    lib.conv1d_epilogue_bwd.argtypes = [vp, vp, vp, vp, vp, sz] + [i] * 5 + [vp]
     lib.conv1d_bwd_weight_noalloc.restype = i
     lib.conv1d_bwd_weight_noalloc.argtypes = [vp, vp, vp] + geom + [i, vp]
     lib.conv1d_set_variant.restype = i
@@ -258,6 +268,23 @@ def conv1d_bwd_weight_noalloc(x, dy, S: int, dilation: int, padding: int, out, s
 
 def conv1d_bwd(x, dy, w, dilation: int, padding: int, out_dx=None, out_dw=None, workspace=None, stream=None):
     """(dx, dw) = both backward passes of the layer in one call -> float32 [N,C,W] and [K,C,S]."""
+    return _bwd(x, dy, w, dilation, padding, out_dx, out_dw, workspace, stream, False)
+
+
+def conv1d_bwd_ex(x, dy, w, dilation: int, padding: int, out_bf16: bool = False):
+    """(dx, dw) of conv1d_bwd, dx stored as bfloat16 when out_bf16, by the kernel where it can."""
+    try:
+        return _bwd(x, dy, w, dilation, padding, None, None, None, None, out_bf16)
+    except Conv1dError as e:
+        if not out_bf16 or e.status != STATUS_EUNSUPPORTED:
+            raise
+    import torch
+
+    dx, dw = conv1d_bwd(x, dy, w, dilation, padding)
+    return dx.to(torch.bfloat16), dw
+
+
+def _bwd(x, dy, w, dilation, padding, out_dx, out_dw, workspace, stream, out_bf16):
     import torch
 
     _dev(x, "x"), _dev(dy, "dy"), _dev(w, "w")
@@ -271,11 +298,47 @@ def conv1d_bwd(x, dy, w, dilation: int, padding: int, out_dx=None, out_dw=None, 
     code = _dtype_code(x)
     need = int(load().conv1d_bwd_workspace_bytes(N, C, K, W, S, dilation, padding, code))
     ws = workspace if workspace is not None else torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-    dx = out_dx if out_dx is not None else torch.empty((N, C, W), dtype=torch.float32, device=x.device)
+    odt = torch.bfloat16 if out_bf16 else torch.float32
+    dx = out_dx if out_dx is not None else torch.empty((N, C, W), dtype=odt, device=x.device)
     dw = out_dw if out_dw is not None else torch.empty((K, C, S), dtype=torch.float32, device=x.device)
-    if tuple(dx.shape) != (N, C, W) or tuple(dw.shape) != (K, C, S) or dx.dtype != torch.float32 or dw.dtype != torch.float32:
+    if tuple(dx.shape) != (N, C, W) or tuple(dw.shape) != (K, C, S) or dx.dtype != odt or dw.dtype != torch.float32:
         raise ValueError("an output has the wrong shape or dtype")
-    _check(load().conv1d_bwd(x.data_ptr(), dy.data_ptr(), w.data_ptr(), _dev(dx, "out_dx").data_ptr(),
-                             _dev(dw, "out_dw").data_ptr(), ws.data_ptr(), ws.numel() * ws.element_size(), N, C, K, W, S,
-                             dilation, padding, code, _stream_ptr(stream)))
+    _check(load().conv1d_bwd_ex(x.data_ptr(), dy.data_ptr(), w.data_ptr(), _dev(dx, "out_dx").data_ptr(),
+                                _dev(dw, "out_dw").data_ptr(), ws.data_ptr(), ws.numel() * ws.element_size(), N, C, K, W, S,
+                                dilation, padding, code, EPI_OUT_BF16 if out_bf16 else 0, _stream_ptr(stream)))
     return dx, dw
+
+
+def conv1d_relu_mask(y):
+    """One bit per element of y, set where it is positive -> uint8 [(numel + 7) // 8]."""
+    import torch
+
+    _dev(y, "y")
+    positive = torch.empty((y.numel() + 7) // 8, dtype=torch.uint8, device=y.device)
+    _check(load().conv1d_relu_mask(y.data_ptr(), positive.data_ptr(), y.numel(), _dtype_code(y), _stream_ptr(None)))
+    return positive
+
+
+def conv1d_epilogue_bwd(gy, positive, dtype, want_bias: bool):
+    """(dy, dbias): gy where `positive` (a conv1d_relu_mask, or None) is set, in `dtype`, and its sum over n, q in float32
+    (None unless wanted).  dy is gy itself where there is nothing to do to it."""
+    import torch
+
+    _dev(gy, "gy")
+    N, K, Q = gy.shape
+    if positive is not None and positive.numel() != (gy.numel() + 7) // 8:
+        raise ValueError("the mask is not one of a tensor of gy's size")
+    same = positive is None and gy.dtype == dtype
+    dy = gy if same else torch.empty(gy.shape, dtype=dtype, device=gy.device)
+    db = ws = None
+    need = 0
+    if want_bias:
+        db = torch.empty(K, dtype=torch.float32, device=gy.device)
+        need = int(load().conv1d_epilogue_bwd_workspace_bytes(N, K, Q))
+        ws = torch.empty(need, dtype=torch.uint8, device=gy.device)
+    if want_bias or not same:
+        _check(load().conv1d_epilogue_bwd(gy.data_ptr(), None if positive is None else positive.data_ptr(),
+                                          None if same else dy.data_ptr(), db.data_ptr() if want_bias else None,
+                                          ws.data_ptr() if want_bias else None, need, N, K, Q, _dtype_code(gy),
+                                          _dtype_code(dy), _stream_ptr(None)))
+    return dy, db

@@ -266,16 +266,32 @@ size_t conv1d_bwd_workspace_bytes(int N, int C, int K, int W, int S, int dilatio
 int conv1d_bwd(const void* x, const void* dy, const void* w, float* dx, float* dw, void* workspace,
                size_t workspace_bytes, int N, int C, int K, int W, int S, int dilation, int padding, int dtype,
                void* stream) {
+    return conv1d_bwd_ex(x, dy, w, dx, dw, workspace, workspace_bytes, N, C, K, W, S, dilation, padding, dtype, 0, stream);
+}
+
+int conv1d_bwd_ex(const void* x, const void* dy, const void* w, void* dx, float* dw, void* workspace,
+                  size_t workspace_bytes, int N, int C, int K, int W, int S, int dilation, int padding, int dtype,
+                  int flags, void* stream) {
     Geom g;
     if (!x || !dy || !w || !dx || !dw || (dtype != CONV1D_FP32 && dtype != CONV1D_BF16)) return CONV1D_EINVAL;
+    if (flags & ~CONV1D_EPI_OUT_BF16) return CONV1D_EINVAL;
+    const bool out_bf16 = flags & CONV1D_EPI_OUT_BF16;
+    if (out_bf16 && dtype != CONV1D_BF16) return CONV1D_EINVAL;
     if (!make_geom(N, C, K, W, S, dilation, padding, &g)) return CONV1D_EINVAL;
     const size_t ea = dtype == CONV1D_BF16 ? 2 : 4;
-    if (!aligned(x, ea) || !aligned(dy, ea) || !aligned(w, ea) || !aligned(dx, 4) || !aligned(dw, 4)) return CONV1D_EINVAL;
+    if (!aligned(x, ea) || !aligned(dy, ea) || !aligned(w, ea) || !aligned(dx, out_bf16 ? 2 : 4) || !aligned(dw, 4)) return CONV1D_EINVAL;
     const size_t need = conv1d_bwd_weight_workspace_bytes(N, C, K, W, S, dilation, padding, dtype);
     if (!workspace || workspace_bytes < need) return CONV1D_EWORKSPACE;
     if (!aligned(workspace, 256)) return CONV1D_EINVAL;
     const int bf16 = dtype == CONV1D_BF16;
-    CorrProblem cp = bwd_data_problem(g, dy, w, dx, bf16);
+    CorrProblem cp = bwd_data_problem(g, dy, w, static_cast<float*>(dx), bf16);
+    if (out_bf16) {
+        // a layer whose passes over channel blocks meet in a float output would change to the plain FMA kernel: the
+        // caller is better off with floats and a conversion
+        const int family = pick_corr(cp);
+        cp.epi.out_bf16 = 1;
+        if (pick_corr(cp) != family) return CONV1D_EUNSUPPORTED;
+    }
     WgradProblem wp = wgrad_problem(g, x, dy, dw, workspace, workspace_bytes, bf16);
     const int corr_family = pick_corr(cp), wgrad_family = pick_wgrad(wp);
     if (corr_family < 0 || wgrad_family < 0) return CONV1D_EUNSUPPORTED;
@@ -310,6 +326,35 @@ int conv1d_bwd_weight_noalloc(const void* x, const void* dy, float* dw, int N, i
     // nothing has to start at zero: every kernel family writes each partial sum before its second stage reads it
     return run_wgrad(g, x, dy, dw, ws, CONV1D_NOALLOC_SCRATCH_BYTES, dtype, stream);
 }
+
+int conv1d_relu_mask(const void* y, void* positive, size_t count, int dtype, void* stream) {
+    if (!y || !positive || (dtype != CONV1D_FP32 && dtype != CONV1D_BF16)) return CONV1D_EINVAL;
+    if (count < 1 || count >> 62 || !aligned(y, dtype == CONV1D_BF16 ? 2 : 4)) return CONV1D_EINVAL;
+    const hipError_t e = relu_mask_launch(y, dtype == CONV1D_BF16, static_cast<unsigned char*>(positive), static_cast<long>(count),
+                                          static_cast<hipStream_t>(stream));
+    if (e == hipErrorInvalidValue) return CONV1D_EUNSUPPORTED;
+    return e == hipSuccess ? CONV1D_OK : CONV1D_EHIP;
+}
+
+size_t conv1d_epilogue_bwd_workspace_bytes(int N, int K, int Q) {
+    return N < 1 || K < 1 || Q < 1 ? 0 : epilogue_grad_workspace(N, K, Q);
+}
+
+int conv1d_epilogue_bwd(const void* gy, const void* positive, void* dy, float* dbias, void* workspace, size_t workspace_bytes,
+                        int N, int K, int Q, int gy_dtype, int dy_dtype, void* stream) {
+    if (!gy || (!dy && !dbias) || N < 1 || K < 1 || Q < 1) return CONV1D_EINVAL;
+    if ((gy_dtype != CONV1D_FP32 && gy_dtype != CONV1D_BF16) || (dy_dtype != CONV1D_FP32 && dy_dtype != CONV1D_BF16)) return CONV1D_EINVAL;
+    if (gy_dtype == CONV1D_BF16 && dy_dtype != CONV1D_BF16) return CONV1D_EINVAL;
+    if (!aligned(gy, gy_dtype == CONV1D_BF16 ? 2 : 4) || !aligned(dy, dy_dtype == CONV1D_BF16 ? 2 : 4) || !aligned(dbias, 4)) return CONV1D_EINVAL;
+    if (dbias && (!workspace || workspace_bytes < epilogue_grad_workspace(N, K, Q))) return CONV1D_EWORKSPACE;
+    if (!aligned(workspace, 4)) return CONV1D_EINVAL;
+    const hipError_t e = epilogue_grad_launch(gy, gy_dtype == CONV1D_BF16, static_cast<const unsigned char*>(positive), dy,
+                                              dy_dtype == CONV1D_BF16, dbias, static_cast<float*>(workspace), N, K, Q,
+                                              static_cast<hipStream_t>(stream));
+    if (e == hipErrorInvalidValue) return CONV1D_EUNSUPPORTED;
+    return e == hipSuccess ? CONV1D_OK : CONV1D_EHIP;
+}
+
 int conv1d_set_variant(int variant) {
     if (variant < CONV1D_VARIANT_AUTO || variant > CONV1D_VARIANT_IGEMM) return CONV1D_EINVAL;
     g_variant.store(variant, std::memory_order_relaxed);

@@ -163,6 +163,13 @@ bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
 bool split_f32_wgrad_supported(const WgradProblem& p);
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken);
 
+// backward of the fused epilogue: one bit per element of a ReLU's output (element i: bit i & 7 of byte i >> 3), and the masked
+// gradient (in dy unless dy is null) with its sum per filter (in dbias unless that is null)
+size_t epilogue_grad_workspace(int N, int K, int Q);
+hipError_t relu_mask_launch(const void* y, int bf16, unsigned char* positive, long n, hipStream_t st);
+hipError_t epilogue_grad_launch(const void* gy, int in16, const unsigned char* positive, void* dy, int out16, float* dbias, float* ws,
+                                int N, int K, int Q, hipStream_t st);
+
 // channel-blocked MFMA family
 bool igemm_corr_supported(const CorrProblem& p);
 hipError_t igemm_corr_launch(const CorrProblem& p, hipStream_t st);
