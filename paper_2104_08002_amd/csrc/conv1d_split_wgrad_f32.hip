@@ -1,28 +1,34 @@
 // FP32 backward-weight on the bf16 matrix instructions (each float the sum of three bfloat16 numbers, a product the six
-// largest of their nine products; see conv1d_split_f32.hip).  Bound by splitting and the latency of the unit loads with few
-// taps, by matrix instructions at half rate with many: N = 8, C = K = 64, W = 20000, both stages, FP32 instruction and three
-// parts: S = 5, d = 1 166 and 98 us, S = 33, d = 4 454 and 222 us, S = 51, d = 8 636 and 330 us.
+// largest of their nine products; see conv1d_split_f32.hip).
 //
 // The contraction runs over positions: A = dy (16 filters x 32 positions), B = x shifted by the tap (32 positions x 16
-// channels).  x sits in LDS as [part][position] rows of 16 channels and is read with the transposing LDS read, so a
-// tap is a row offset whatever the dilation; dy sits in operand order.  A workgroup (8 waves, one per CU) owns a strip
-// of units of QC positions, 16 FBW filters, 16 channels and TW NTW taps; wave v owns NTW of those taps and every
-// WK-th k-step of 32 positions (TW WK = 8), and the WK sums of a tap are added in a fixed order.  Units are
-// double-buffered in LDS with their loads one unit ahead in registers; half of the waves split and write the next unit
-// before they multiply, the other half after, so that the matrix units have work meanwhile.
+// channels).  x sits in LDS as [part][8 channels][position] and is read with the transposing LDS read, so a tap is a row
+// offset whatever the dilation; dy sits in operand order.  A workgroup (one per CU) owns a strip of units of QC positions,
+// 16 filters, 16 channels and TW NTW taps.  Eight of its waves multiply: wave v owns NTW of the taps and every WK-th
+// k-step of 32 positions (TW WK = 8), and the WK sums of a tap are added in a fixed order.  The other eight load, split and
+// write the next unit meanwhile (two units in LDS, the loads of two more in registers).
 // Partial tiles and second stage are those of the small-channel kernel, ws[(pair * strips + strip) * S + s][16][16].
+//
+// With many taps the matrix instructions bound it, at the clock they are granted with values as dense as these (C = K = 64,
+// S = 33: 1.25 of the 1.33 PFLOP/s that a large product of matrices reaches on such values); with few the loads and the
+// splitting do (S = 5: 62 us, about 55 without the products).  While every wave did both, one filter or two blocks at a time,
+// loads one wave's share of a unit ahead and in lanes that fell on 16 rows (64 cache accesses a load instead of 4) it took, in
+// us, then and now, both stages: N = 8, C = K = 64, W = 20000: S = 5, d = 1 95 and 63, S = 33, d = 4 227 and 212, S = 51, d = 8
+// 341 and 304; N = 16, C = K = 15, W = 60000, S = 51, d = 8 148 and 123; N = 12, C = 24, K = 40, W = 4999, S = 7, d = 3 44 and
+// 21; N = 20, C = K = 48, W = 3001, S = 17, d = 3 64 and 35; N = 8, C = K = 256, W = 2000, S = 3 153 and 90.
 #include "conv1d_split_f32.h"
 
 namespace conv1d {
 namespace {
 using namespace sp;
 
-constexpr int kThreads = 512;
+constexpr int kRole = 512;  // threads that multiply, and as many that stage
 constexpr size_t kLdsAll = 160 * 1024;
-// 16-byte slots of dy and x a thread stages per unit, and register sets: with few products per unit the loads have to be
-// two units ahead to arrive in time (S = 5: 105 us with one set)
-constexpr int kDyTasks = 2, kXTasks = 3;
-constexpr int num_sets(int fbw, int ntw) { return (fbw == 1 && ntw <= 9) || fbw * ntw <= 6 ? 2 : 1; }
+constexpr int kMaxUnit = kRole / 2;  // positions: a staging thread has one 16-byte slot of dy
+constexpr int kXTasks = 3;           // and at most so many of x
+// Two running sums of a tap, one for every other unit, where the registers allow: half as many roundings of each.
+constexpr bool two_sums(int ntw) { return ntw <= 7; }
+constexpr bool four_steps(int ntw) { return ntw <= 9 && ntw != 7; }  // dy of four k-steps fits beside the sums
 
 struct SwfArgs {
     const float* x;
@@ -30,9 +36,10 @@ struct SwfArgs {
     float* ws;
     int C, K, W, Q, S, d, P;
     long x_sn, dy_sn;
-    int qc_sh, upr, nunits, strips, tw_sh, tgroups, kgroups, cblocks, lx, vec;
+    int N, qc, upr, nunits, strips, tw_sh, tgroups, kblocks, cblocks, lx, lxp;
 };
 
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_at4;  // four floats from any float on
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 __device__ __forceinline__ u32x2 read_tr(const u32x2* p) {
@@ -45,295 +52,333 @@ __device__ __forceinline__ void opaque(int& v) {
 #endif
 }
 
-template <int FBW, int NTW>
-__global__ __launch_bounds__(kThreads, 2) void split_wgrad_f32_kernel(SwfArgs a) {
+// XT: slots of x of a staging thread
+template <int NTW, int XT>
+__global__ __launch_bounds__(2 * kRole, 4) void split_wgrad_f32_kernel(SwfArgs a) {
     extern __shared__ u32x4 lds[];
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int QC = 1 << a.qc_sh, TW = 1 << a.tw_sh, WK = 8 >> a.tw_sh;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+    const int block_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = threadIdx.x & (kRole - 1), wave = block_wave & 7;
+    const int QC = a.qc, TW = 1 << a.tw_sh, WK = 8 >> a.tw_sh;
     const int tw = wave & (TW - 1), wk = wave >> a.tw_sh;
-    const int ndy = FBW * QC * 2, nx = 2 * a.lx;   // 16-byte slots per part
+    const int ndy = QC * 2, nx = 2 * a.lxp;   // 16-byte slots per part
     const int stage = 3 * (ndy + nx);
 
     int id = xcd_logical_id(blockIdx.x, gridDim.x);
     const int cb = id % a.cblocks;
     id /= a.cblocks;
-    const int kg = id % a.kgroups;
-    id /= a.kgroups;
+    const int kb = id % a.kblocks;
+    id /= a.kblocks;
     const int tg = id % a.tgroups, strip = id / a.tgroups;
-    const int k0 = kg * 16 * FBW, c0 = cb * 16, s0 = tg * (NTW << a.tw_sh);
+    const int k0 = kb * 16, c0 = cb * 16, s0 = tg * (NTW << a.tw_sh);
     const int u_begin = static_cast<int>(static_cast<long>(strip) * a.nunits / a.strips);
     const int u_end = static_cast<int>(static_cast<long>(strip + 1) * a.nunits / a.strips);
 
-    constexpr int NSET = num_sets(FBW, NTW);
+    // Loads are issued without a branch, where lanes have nothing to load too: the compiler counts them to wait for the
+    // older ones alone, and past a branch it waits for all.  Consecutive lanes load consecutive positions (64 lanes in 16
+    // rows take the cache 64 accesses).
     struct Set {
-        float dv[kDyTasks][8], xv[kXTasks][8];
+        float dv[8], xv[XT][8];
     };
-    Set sets[NSET];
-    // byte offsets in a sample, which the plan keeps below 2^32: uniform base + 32-bit offset, one register per row
-    unsigned xrow[8], dyrow[kDyTasks];
+    Set sets[2];
+    // byte offsets in a sample, which the plan keeps below 2^32
+    const int half = wave >> 2, xpos = tid & 255;  // this thread's 8 channels and its first position
+    unsigned xrow[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) xrow[e] = 4u * static_cast<unsigned>(min(c0 + 8 * (tid & 1) + e, a.C - 1) * a.W);
-#pragma unroll
-    for (int k = 0; k < kDyTasks; ++k) {
-        const int f = min(tid + k * kThreads, ndy - 1) >> (a.qc_sh + 1);
-        dyrow[k] = 4u * static_cast<unsigned>(min(k0 + 16 * f + (tid & 15), a.K - 1) * a.Q);
-    }
+    for (int e = 0; e < 8; ++e) xrow[e] = 4u * static_cast<unsigned>(min(c0 + 8 * half + e, a.C - 1) * a.W);
+    const int dyi = min(tid, ndy - 1), dym = dyi / (QC / 8), dyj = dyi - dym * (QC / 8);  // filter, and which 8 of 32 positions
+    const unsigned dyrow = 4u * static_cast<unsigned>(min(k0 + dym, a.K - 1) * a.Q);
+    const int dyq = 32 * (dyj >> 2) + 4 * (dyj & 3);
+    // the filters of a position are turned by it, so that neither the lanes that write (positions) nor those that read
+    // (filters) meet in a bank
+    const int dyslot = dyj * 16 + ((dym ^ dyj) & 15);
+    const bool whole_rows = k0 + 16 <= a.K, whole_channels = c0 + 16 <= a.C;
+    // a row's last loads go on into the next row, the tensor's last ones begin up to 3 elements early
+    const unsigned dyend = 4u * static_cast<unsigned>(a.K * a.Q - 4);
+    auto dy_offset = [&](int q) { return dyrow + 4u * static_cast<unsigned>(min(q, a.Q - 1)); };
     auto request = [&](int u, Set& set) __attribute__((always_inline)) {
-        auto& dv = set.dv;
-        auto& xv = set.xv;
-        const int n = u / a.upr, q0 = (u - n * a.upr) << a.qc_sh;
+        const int n = u / a.upr, q0 = (u - n * a.upr) * QC;
         const char* dyb = reinterpret_cast<const char*>(a.dy + n * a.dy_sn);
         const char* xb = reinterpret_cast<const char*>(a.x + n * a.x_sn);
+        const unsigned last = n == a.N - 1 ? dyend : 0xffffffffu;
 #pragma unroll
-        for (int k = 0; k < kDyTasks; ++k) {
-            if (k * kThreads >= ndy) break;
-            const int j = (min(tid + k * kThreads, ndy - 1) >> 4) & (QC / 8 - 1);
-            const int q = q0 + 32 * (j >> 2) + 4 * (j & 3);
-            if (a.vec) {
+        for (int h = 0; h < 2; ++h) {
+            const f32x4_at4 v = *reinterpret_cast<const f32x4_at4*>(dyb + min(dy_offset(q0 + dyq + 16 * h), last));
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(dyb + (dyrow[k] + 4u * min(q + 16 * h, a.Q - 4)));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dv[k][4 * h + e] = v[e];
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    dv[k][e] = *reinterpret_cast<const float*>(dyb + (dyrow[k] + 4u * min(q + 16 * (e >> 2) + (e & 3), a.Q - 1)));
-            }
+            for (int e = 0; e < 4; ++e) set.dv[4 * h + e] = v[e];
         }
         const int col0 = q0 + s0 * a.d - a.P;
 #pragma unroll
-        for (int k = 0; k < kXTasks; ++k) {
-            if (k * kThreads >= nx) break;
-            const unsigned col = 4u * clampi(col0 + min((tid + k * kThreads) >> 1, a.lx - 1), 0, a.W - 1);
+        for (int k = 0; k < XT; ++k) {
+            const unsigned col = 4u * static_cast<unsigned>(clampi(col0 + min(xpos + 256 * k, a.lx - 1), 0, a.W - 1));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xv[k][e] = *reinterpret_cast<const float*>(xb + (xrow[e] + col));
+            for (int e = 0; e < 8; ++e) set.xv[k][e] = *reinterpret_cast<const float*>(xb + (xrow[e] + col));
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto park = [&](int u, u32x4* b, Set& set) __attribute__((always_inline)) {
-        auto& dv = set.dv;
-        auto& xv = set.xv;
-        const int n = u / a.upr, q0 = (u - n * a.upr) << a.qc_sh;
+    auto park = [&](int u, u32x4* b, const Set& set) __attribute__((always_inline)) {
+        const int n = u / a.upr, q0 = (u - n * a.upr) * QC;
         // The matrix instruction cuts sums off towards minus infinity, which adds up over millions of terms: every other
         // unit of the layer is multiplied with -dy and subtracted, so that the offsets cancel, within a strip or, where
         // strips have a unit or two, between them.  (Counted from the strip's first unit they did not cancel in strips of
         // one: C = K = 15, S = 7, 66000 columns of 80 % zeros 3.6e-7 of the gradient, FP32 instruction 1.8e-7.)
         const unsigned sign = (u & 1) ? 0x80000000u : 0u;
+        const bool early = n == a.N - 1 && q0 + QC > a.Q - 4;
+        const bool dy_inside = whole_rows && q0 + QC <= a.Q;
+        if (64 * wave < ndy) {
+            const int q = q0 + dyq;
+            float v[8];
 #pragma unroll
-        for (int k = 0; k < kDyTasks; ++k) {
-            const int i = tid + k * kThreads;
-            if (i < ndy) {
-                const int j = (i >> 4) & (QC / 8 - 1), f = i >> (a.qc_sh + 1);
-                const int left = k0 + 16 * f + (i & 15) < a.K ? a.Q - (q0 + 32 * (j >> 2) + 4 * (j & 3)) : 0;
+            for (int e = 0; e < 8; ++e) v[e] = set.dv[e];
+            if (early) {
+#pragma unroll
+                for (int h = 0; h < 8; h += 4) {
+                    const unsigned off = dy_offset(q + 4 * h);
+                    const unsigned sh = off > dyend ? (off - dyend) >> 2 : 0u;
+                    v[h] = sh & 1 ? v[h + 1] : v[h];
+                    v[h + 1] = sh & 1 ? v[h + 2] : v[h + 1];
+                    v[h + 2] = sh & 1 ? v[h + 3] : v[h + 2];
+                    v[h] = sh & 2 ? v[h + 2] : v[h];
+                    v[h + 1] = sh & 2 ? v[h + 3] : v[h + 1];
+                }
+            }
+            if (!dy_inside) {
+                const int left = k0 + dym < a.K ? a.Q - q : 0;
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    dv[k][e] = 16 * (e >> 2) + (e & 3) >= left ? 0.f : __uint_as_float(__float_as_uint(dv[k][e]) ^ sign);
-                const Split8 s = split8(dv[k]);
-                b[i] = s.h;
-                b[ndy + i] = s.m;
-                b[2 * ndy + i] = s.l;
+                    if (16 * (e >> 2) + (e & 3) >= left) v[e] = 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ sign);
+            const Split8 s = split8(v);
+            u32x4* o = b + dyslot;
+            if (tid < ndy) {
+                o[0] = s.h;
+                o[ndy] = s.m;
+                o[2 * ndy] = s.l;
             }
         }
-        u32x4* xs = b + 3 * ndy;
+        u32x4* xs = b + 3 * ndy + half * a.lxp;
         const int col0 = q0 + s0 * a.d - a.P;
+        const bool x_inside = whole_channels && col0 >= 0 && col0 + a.lx <= a.W;
 #pragma unroll
-        for (int k = 0; k < kXTasks; ++k) {
-            const int i = tid + k * kThreads;
-            if (i < nx) {
-                const int col = col0 + (i >> 1);
-                const int cleft = (col >= 0 && col < a.W) ? a.C - c0 - 8 * (i & 1) : 0;
+        for (int k = 0; k < XT; ++k) {
+            if (64 * (wave & 3) + 256 * k >= a.lx) break;
+            const int pos = xpos + 256 * k, col = col0 + pos;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = set.xv[k][e];
+            if (!x_inside) {
+                const int cleft = (col >= 0 && col < a.W) ? a.C - c0 - 8 * half : 0;
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    if (e >= cleft) xv[k][e] = 0.f;
-                const Split8 s = split8(xv[k]);
-                xs[i] = s.h;
-                xs[nx + i] = s.m;
-                xs[2 * nx + i] = s.l;
+                    if (e >= cleft) v[e] = 0.f;
+            }
+            const Split8 s = split8(v);
+            if (pos < a.lx) {
+                xs[pos] = s.h;
+                xs[nx + pos] = s.m;
+                xs[2 * nx + pos] = s.l;
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    f32x4 acc[NTW][FBW];
+    // f(unit, its place in the strip modulo 2) and a barrier, over the strip.  (With a way out in the middle of the loop the
+    // compiler could not count the loads either.)
+    auto each_unit = [&](auto f) __attribute__((always_inline)) {
+        int u = u_begin;
+        for (; u + 1 < u_end; u += 2) {
+            f(u, std::integral_constant<int, 0>{});
+            __syncthreads();
+            f(u + 1, std::integral_constant<int, 1>{});
+            __syncthreads();
+        }
+        if (u < u_end) {
+            f(u, std::integral_constant<int, 0>{});
+            __syncthreads();
+        }
+    };
+    if (block_wave >= 8) {
+        request(u_begin, sets[0]);
+        request(min(u_begin + 1, u_end - 1), sets[1]);
+        park(u_begin, lds, sets[0]);
+        request(min(u_begin + 2, u_end - 1), sets[0]);
+        __syncthreads();
+        each_unit([&](int u, auto par) __attribute__((always_inline)) {
+            constexpr int PAR = decltype(par)::value;
+            Set& set = sets[1 - PAR];
+            if (u + 1 < u_end) park(u + 1, lds + (1 - PAR) * stage, set);
+            request(min(u + 3, u_end - 1), set);
+        });
+        return;  // (a barrier does not wait for waves that have ended)
+    }
+
+    // Running sums of a tap; sums[1] is that of every other unit, whose products have the other sign.  Their roundings are
+    // what the error of a gradient is made of, so up to four k-steps are summed by themselves first (C = K = 64, S = 33, d = 4,
+    // W = 20000, N = 8: 2.4e-7 with an addition per k-step, now 1.6e-7; as one chain of matrix instructions, which cut off at the
+    // size of the sum so far, 2.1e-7).
+    constexpr int NS = two_sums(NTW) ? 2 : 1;
+    f32x4 sums[NS][NTW];
 #pragma unroll
     for (int i = 0; i < NTW; ++i)
 #pragma unroll
-        for (int f = 0; f < FBW; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < NS; ++s) sums[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // unit u, the PAR-th of the strip modulo 2
-    auto unit = [&](int u, auto par) __attribute__((always_inline)) {
+    // rows of 8 channels, two planes: this lane's piece of rows 4 g .. 4 g + 3
+    const int piece = 2 * (((l16 >> 1) & 1) * a.lxp + 4 * g + (l16 >> 2)) + (l16 & 1);
+    __syncthreads();
+    each_unit([&](int, auto par) __attribute__((always_inline)) {
         constexpr int PAR = decltype(par)::value;
         const u32x4* cur = lds + PAR * stage;
-        auto refill = [&] {
-            Set& set = sets[(PAR + 1) % NSET];
-            if (u + 1 < u_end) park(u + 1, lds + (1 - PAR) * stage, set);
-            if (u + 1 + NSET < u_end) request(u + 1 + NSET, set);
-        };
-        if (wave & 4) refill();
-        const u32x4* dys = cur + g * 16 + l16;
-        // rows of 16 channels are 4 transposing reads wide: this lane's piece of rows 4 g .. 4 g + 3
-        const int xs0 = 2 * (PAR * stage + 3 * ndy) + (4 * g + (l16 >> 2)) * 4 + (l16 & 3) + tw * NTW * a.d * 4;
-        for (int ks = wk; ks < QC / 32; ks += WK) {
-            u32x4 y[FBW][3];
+        const int xs0 = 2 * (PAR * stage + 3 * ndy + tw * NTW * a.d);
+        // H k-steps, WK apart
+        auto steps = [&](int ks, auto count) __attribute__((always_inline)) {
+            constexpr int H = decltype(count)::value;
+            u32x4 y[H][3];
+            int at = piece, mine = g;
+            opaque(at);  // or addresses of every copy of this code are kept in registers of their own
+            opaque(mine);
 #pragma unroll
-            for (int f = 0; f < FBW; ++f)
+            for (int h = 0; h < H; ++h) {
+                const int row = 4 * (ks + h * WK) + mine;
 #pragma unroll
-                for (int i = 0; i < 3; ++i) y[f][i] = dys[i * ndy + f * (QC * 2) + ks * 64];
-            // U taps at a time: the reads of the next ones are issued in front of the products of these, and no earlier
-            // (left to itself the compiler reads further ahead and spills)
-            constexpr int U = FBW == 1 ? 2 : 1;
-            u32x4 b[2][U][3];
-            int at = xs0 + 128 * ks;
-            auto read = [&](int t) {
+                for (int i = 0; i < 3; ++i) y[h][i] = cur[i * ndy + row * 16 + ((l16 ^ row) & 15)];
+            }
+            // the next reads are issued in front of the products of these, and no earlier (left to itself the compiler reads
+            // further ahead and spills)
+            u32x4 b[2][3];
+            at += xs0 + 64 * ks;
+            auto read = [&](int r) {
 #pragma unroll
-                for (int v = 0; v < U; ++v)
-                    if (t + v < NTW) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            const u32x2* p = reinterpret_cast<const u32x2*>(lds) + at + i * 2 * nx;
-                            const u32x2 lo = read_tr(p), hi = read_tr(p + 64);
-                            b[(t / U) & 1][v][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                        }
-                        at += 4 * a.d;
-                        opaque(at);  // one running index, not one register per tap and part
-                    }
+                for (int i = 0; i < 3; ++i) {
+                    const u32x2* p = reinterpret_cast<const u32x2*>(lds) + at + i * 2 * nx;
+                    const u32x2 lo = read_tr(p), hi = read_tr(p + 32);
+                    b[r & 1][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                }
+                // one running index, not one register per tap and part
+                at += r % H == H - 1 ? 2 * a.d - 64 * WK * (H - 1) : 64 * WK;
+                opaque(at);
             };
             read(0);
+            f32x4 total;
 #pragma unroll
-            for (int t = 0; t < NTW; t += U) {
-                if (t + U < NTW) read(t + U);
+            for (int r = 0; r < H * NTW; ++r) {
+                if (r + 1 < H * NTW) read(r + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                f32x4 part[U][FBW];
+                const int t = r / H, h = r % H;
+                f32x4 part = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int k = 0; k < 6; ++k)
-#pragma unroll
-                    for (int v = 0; v < U; ++v)
-                        if (t + v < NTW)
-#pragma unroll
-                            for (int f = 0; f < FBW; ++f)
-                                part[v][f] = mfma(y[f][kPartB[k]], b[(t / U) & 1][v][kPartA[k]], k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[v][f]);
-#pragma unroll
-                for (int v = 0; v < U; ++v)
-                    if (t + v < NTW)
-#pragma unroll
-                        for (int f = 0; f < FBW; ++f) acc[t + v][f] = PAR ? acc[t + v][f] - part[v][f] : acc[t + v][f] + part[v][f];
+                for (int k = 0; k < 6; ++k) part = mfma(y[h][kPartB[k]], b[r & 1][kPartA[k]], part);
+                total = h == 0 ? part : total + part;
+                if (h == H - 1) {
+                    f32x4& sum = sums[PAR % NS][t];
+                    sum = NS == 1 && PAR ? sum - total : sum + total;
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
-        }
-        if (!(wave & 4)) refill();
-        __syncthreads();
-    };
-    if (u_begin < u_end) {
-        request(u_begin, sets[0]);
-        if (NSET == 2 && u_begin + 1 < u_end) request(u_begin + 1, sets[NSET - 1]);
-        park(u_begin, lds, sets[0]);
-        if (u_begin + NSET < u_end) request(u_begin + NSET, sets[0]);
-    }
-    __syncthreads();
-    for (int u = u_begin; u < u_end; u += 2) {
-        unit(u, std::integral_constant<int, 0>{});
-        if (u + 1 < u_end) unit(u + 1, std::integral_constant<int, 1>{});
-    }
+        };
+        int ks = wk;
+        if constexpr (four_steps(NTW))
+            for (; ks + 3 * WK < QC / 32; ks += 4 * WK) steps(ks, std::integral_constant<int, 4>{});
+        for (; ks + WK < QC / 32; ks += 2 * WK) steps(ks, std::integral_constant<int, 2>{});
+        if (ks < QC / 32) steps(ks, std::integral_constant<int, 1>{});
+    });
+    f32x4 acc[NTW];
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) acc[i] = NS == 2 ? sums[0][i] - sums[NS - 1][i] : sums[0][i];
 
     // the k-step shares of a tap, left to right
     f32x4* red = reinterpret_cast<f32x4*>(lds);
     for (int r = 1; r < WK; ++r) {
         if (wk == r)
 #pragma unroll
-            for (int i = 0; i < NTW; ++i)
-#pragma unroll
-                for (int f = 0; f < FBW; ++f) red[((tw * NTW + i) * FBW + f) * 64 + lane] = acc[i][f];
+            for (int i = 0; i < NTW; ++i) red[(tw * NTW + i) * 64 + lane] = acc[i];
         __syncthreads();
         if (wk == 0)
 #pragma unroll
-            for (int i = 0; i < NTW; ++i)
-#pragma unroll
-                for (int f = 0; f < FBW; ++f) acc[i][f] += red[((tw * NTW + i) * FBW + f) * 64 + lane];
+            for (int i = 0; i < NTW; ++i) acc[i] += red[(tw * NTW + i) * 64 + lane];
         __syncthreads();
     }
     if (wk != 0) return;
     const float turn = (u_begin & 1) ? -1.f : 1.f;  // such a strip added up its units with the opposite sign
+    float* ws = a.ws + (static_cast<long>(kb * a.cblocks + cb) * a.strips + strip) * a.S * 256;
 #pragma unroll
-    for (int f = 0; f < FBW; ++f) {
-        const int kb = kg * FBW + f;
-        if (16 * kb >= a.K) continue;
-        float* ws = a.ws + (static_cast<long>(kb * a.cblocks + cb) * a.strips + strip) * a.S * 256;
+    for (int i = 0; i < NTW; ++i) {
+        const int s = s0 + tw * NTW + i;
+        if (s < a.S)
 #pragma unroll
-        for (int i = 0; i < NTW; ++i) {
-            const int s = s0 + tw * NTW + i;
-            if (s < a.S)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) ws[s * 256 + (4 * g + j) * 16 + l16] = turn * acc[i][f][j];
-        }
+            for (int j = 0; j < 4; ++j) ws[s * 256 + (4 * g + j) * 16 + l16] = turn * acc[i][j];
     }
 }
 
 struct Plan {
     bool ok;
-    int fbw, ntw, grid;
+    int ntw, grid;
     SwfArgs a;
     size_t lds;
 };
 
-constexpr int kShapes[][2] = {{1, 3}, {1, 5}, {1, 7}, {1, 9}, {1, 13}, {2, 2}, {2, 3}, {2, 5}, {2, 7}, {2, 9}, {4, 2}, {4, 3}};
+// positions of a plane of 8 channels, rounded up so that the two planes of a read begin in different halves of the banks
+long padded(long lx) { return ((lx + 7) & ~15L) + 8; }
+
+// taps of a wave, within the 128 registers of 16 waves
+constexpr int kTaps[] = {3, 5, 7, 9, 13};
 
 Plan make_plan(const WgradProblem& p) {
     Plan best{};
     if (p.bf16 || p.dw_sc != p.S || static_cast<long>(p.N) * p.Q < kMinTerms) return best;
+    if (static_cast<long>(p.K) * p.Q < 4) return best;  // dy is loaded by four elements of a sample
     const size_t wsb = smallc_wgrad_f32_blocks_workspace(p);  // the partial tiles take no more than that kernel's
     if (wsb == 0) return best;
     const int cblocks = cdiv(p.C, 16), kblocks = cdiv(p.K, 16);
     const long most = static_cast<long>(wsb / (static_cast<size_t>(cblocks) * kblocks * p.S * 1024));
     double best_cost = 0;
-    constexpr int kUnitSizes = 5;  // units of 32 << i positions
-    struct {
-        int upr;
-        long nunits, strips;
-        double longest;  // units of the longest strip
-    } cut[kUnitSizes];
-    for (int i = 0; i < kUnitSizes; ++i) {
-        auto& c = cut[i];
-        c.upr = cdiv(p.Q, 32 << i);
-        c.nunits = static_cast<long>(p.N) * c.upr;
-        c.strips = most < c.nunits ? most : c.nunits;
-        c.longest = c.strips < 1 ? 0.0 : static_cast<double>((c.nunits + c.strips - 1) / c.strips);
-    }
-    for (const auto& sh : kShapes) {
-        const int fbw = sh[0], ntw = sh[1];
-        if (fbw > 1 && ntw > 2 && fbw / 2 >= kblocks) continue;  // half the filter blocks would do: such a shape loses anyway
-        const int kgroups = cdiv(kblocks, fbw);
+    for (const int ntw : kTaps) {
         for (int tw_sh = 0; tw_sh <= 3; ++tw_sh) {
             const int taps = ntw << tw_sh, tgroups = cdiv(p.S, taps), WK = 8 >> tw_sh;
-            const long per_strip = static_cast<long>(cblocks) * kgroups * tgroups;
-            for (int i = 3 - tw_sh; i < kUnitSizes; ++i) {  // a k-step at least for every wave of a tap
-                const int qc_sh = 5 + i, QC = 1 << qc_sh;
-                const auto& c = cut[i];
-                const long lx = QC + static_cast<long>(taps - 1) * p.d;
-                const long ndy = static_cast<long>(fbw) * QC * 2;
-                const size_t stage = static_cast<size_t>(3 * (ndy + 2 * lx)) * 16;
-                const size_t red = WK > 1 ? static_cast<size_t>(taps) * fbw * 1024 : 0;
+            if (tw_sh > 0 && tgroups == cdiv(p.S, taps / 2)) continue;  // half the waves would do
+            const long per_strip = static_cast<long>(cblocks) * kblocks * tgroups;
+            const long halo = static_cast<long>(taps - 1) * p.d;
+            // units whose x is one, two or three positions per staging thread, and small ones for short rows
+            for (int i = 0; i < 6; ++i) {
+                long QC = i < 3 ? ((i + 1) * (kRole / 2) - halo) & ~31L : 32L << (i - 3);
+                const long fits = (static_cast<long>(kLdsAll / 96) - 2 * (halo + 23)) / 4;  // 2 stages of 3 parts
+                if (QC > fits) QC = fits & ~31L;
+                if (QC > kMaxUnit) QC = kMaxUnit;
+                if (QC < 32) continue;
+                const long lx = QC + halo, lxp = padded(lx);
+                const size_t stage = static_cast<size_t>(3 * (2 * QC + 2 * lxp)) * 16;
+                const size_t red = WK > 1 ? static_cast<size_t>(taps) * 1024 : 0;
                 const size_t lds = red > 2 * stage ? red : 2 * stage;
-                if (ndy > kDyTasks * kThreads || 2 * lx > kXTasks * kThreads || lds > kLdsAll) continue;
-                if (c.nunits > 0x3fffffffL || c.strips < 1 || c.strips * per_strip > (1 << 20)) continue;
-                // cycles of a unit on one SIMD's two waves: matrix instructions, LDS reads of all eight, splitting
-                const double steps = QC / 32 >> (3 - tw_sh);
-                const double mm = 2 * steps * ntw * fbw * 96;
-                const double rd = 8 * steps * (3.0 * fbw + 3.0 * ntw) * 8;
-                const double staging = 1500 + (cdiv(ndy, kThreads) + cdiv(2 * lx, kThreads)) * 2 * 300.0;
-                const double unit = (mm > rd ? mm : rd) + 0.5 * staging;
-                const double waves = static_cast<double>((c.strips * per_strip + 255) / 256);
-                const double cost = waves * (unit * c.longest + 10000 + WK * taps * fbw * 16.0);
+                if (2 * lx > kXTasks * kRole || lds > kLdsAll) continue;
+                const int steps = cdiv(QC / 32, WK);
+                // one k-step per addition and one running sum: not over more, shorter units than this
+                if (steps == 1 && !two_sums(ntw) && QC < kMaxUnit && QC < p.Q) continue;
+                const int upr = cdiv(p.Q, QC);
+                const long nunits = static_cast<long>(p.N) * upr;
+                // no more workgroups than CUs (six pairs of blocks in 43 strips each took two turns: 34 instead of 26 us)
+                const long turn = per_strip < 256 ? 256 / per_strip : 1;
+                long strips = most < turn ? most : turn;
+                if (strips > nunits) strips = nunits;
+                if (nunits > 0x3fffffffL || strips < 1 || strips * per_strip > (1 << 20)) continue;
+                const double longest = static_cast<double>((nunits + strips - 1) / strips);  // units of the longest strip
+                // Cycles of a unit on one SIMD, the products of its two multiplying waves beside what its two staging waves
+                // do; a fit to all tiles on 17 layers (C, K 4 ... 256, 1 ... 51 taps): what is taken is within 9 % of the
+                // fastest, 2 % on average.
+                const double mm = steps * (270.0 * ntw + 200.0), staging = 950.0 * (1 + cdiv(2 * lx, kRole));
+                const double unit = mm > staging ? mm + 0.26 * staging : staging + 0.26 * mm;
+                const double waves = static_cast<double>((strips * per_strip + 255) / 256);
+                const double cost = waves * (unit * longest + 11000 + WK * taps * 42.0);
                 if (best.ok && cost >= best_cost) continue;
                 best_cost = cost;
                 best.ok = true;
-                best.fbw = fbw;
                 best.ntw = ntw;
                 best.lds = lds;
-                best.grid = static_cast<int>(c.strips * per_strip);
+                best.grid = static_cast<int>(strips * per_strip);
                 SwfArgs& a = best.a;
-                a.qc_sh = qc_sh; a.upr = c.upr; a.nunits = static_cast<int>(c.nunits); a.strips = static_cast<int>(c.strips);
-                a.tw_sh = tw_sh; a.tgroups = tgroups; a.kgroups = kgroups; a.lx = static_cast<int>(lx);
+                a.qc = static_cast<int>(QC); a.upr = upr; a.nunits = static_cast<int>(nunits); a.strips = static_cast<int>(strips);
+                a.tw_sh = tw_sh; a.tgroups = tgroups; a.lx = static_cast<int>(lx); a.lxp = static_cast<int>(lxp);
             }
         }
     }
@@ -342,19 +387,19 @@ Plan make_plan(const WgradProblem& p) {
     a.x = static_cast<const float*>(p.x);
     a.dy = static_cast<const float*>(p.dy);
     a.ws = static_cast<float*>(p.ws);
-    a.C = p.C; a.K = p.K; a.W = p.W; a.Q = p.Q; a.S = p.S; a.d = p.d; a.P = p.P;
+    a.N = p.N; a.C = p.C; a.K = p.K; a.W = p.W; a.Q = p.Q; a.S = p.S; a.d = p.d; a.P = p.P;
     a.x_sn = p.x_sn; a.dy_sn = p.dy_sn;
-    a.cblocks = cblocks;
-    a.vec = p.Q % 4 == 0 && p.dy_sn % 4 == 0 && (reinterpret_cast<uintptr_t>(p.dy) & 15) == 0;
+    a.cblocks = cblocks; a.kblocks = kblocks;
     return best;
 }
 
-template <int FBW, int NTW>
+template <int NTW>
 hipError_t run(const Plan& pl, hipStream_t st) {
-    auto kern = split_wgrad_f32_kernel<FBW, NTW>;
+    const int xt = cdiv(pl.a.lx, kRole / 2);
+    auto kern = xt == 1 ? split_wgrad_f32_kernel<NTW, 1> : xt == 2 ? split_wgrad_f32_kernel<NTW, 2> : split_wgrad_f32_kernel<NTW, 3>;
     const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), pl.lds);
     if (e != hipSuccess) return e;
-    return launch_kernel(kern, dim3(pl.grid), dim3(kThreads), pl.lds, st, pl.a);
+    return launch_kernel(kern, dim3(pl.grid), dim3(2 * kRole), pl.lds, st, pl.a);
 }
 
 }  // namespace
@@ -363,7 +408,7 @@ bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; 
 
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
     const Plan pl = make_plan(p);
-    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
+    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
     return pl.ok;
 }
 
@@ -372,19 +417,12 @@ hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* t
     *taken = pl.ok;
     if (!pl.ok) return hipSuccess;
     hipError_t e;
-    switch (pl.fbw * 16 + pl.ntw) {
-        case 16 + 3: e = run<1, 3>(pl, st); break;
-        case 16 + 5: e = run<1, 5>(pl, st); break;
-        case 16 + 7: e = run<1, 7>(pl, st); break;
-        case 16 + 9: e = run<1, 9>(pl, st); break;
-        case 16 + 13: e = run<1, 13>(pl, st); break;
-        case 32 + 2: e = run<2, 2>(pl, st); break;
-        case 32 + 3: e = run<2, 3>(pl, st); break;
-        case 32 + 5: e = run<2, 5>(pl, st); break;
-        case 32 + 7: e = run<2, 7>(pl, st); break;
-        case 32 + 9: e = run<2, 9>(pl, st); break;
-        case 64 + 3: e = run<4, 3>(pl, st); break;
-        case 64 + 2: e = run<4, 2>(pl, st); break;
+    switch (pl.ntw) {
+        case 3: e = run<3>(pl, st); break;
+        case 5: e = run<5>(pl, st); break;
+        case 7: e = run<7>(pl, st); break;
+        case 9: e = run<9>(pl, st); break;
+        case 13: e = run<13>(pl, st); break;
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;

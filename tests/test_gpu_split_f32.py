@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
 PASSES = ("fwd", "bwd_data", "bwd_weight")
 
 # pass, tile, N  C  K  W  S  d  P.  tile: filter blocks of 16 and column blocks of 64 of a workgroup, planes of 8 channels of
-# a step; for the weight gradient filter blocks, taps of a wave, units of the longest strip (the CPU test of the library's
+# a step; for the weight gradient one filter block, taps of a wave, units of the longest strip (the CPU test of the library's
 # bounds model checks that these are the tiles taken).  Widths of the output are odd and end inside a tile, filters end
 # inside a block, and groups of filter blocks lack one.
 TILES = [
@@ -48,15 +48,19 @@ TILES = [
     ("bwd_weight", (1, 3, 3),  (43, 4, 4, 3497, 1, 3, 1)),
     ("bwd_weight", (1, 5, 4),  (51, 5, 6, 3856, 4, 3, 0)),
     ("bwd_weight", (1, 7, 2),  (45, 5, 4, 1467, 7, 2, 6)),
-    ("bwd_weight", (1, 9, 3),  (47, 6, 4, 3117, 9, 5, 0)),
-    ("bwd_weight", (1, 13, 4), (55, 6, 6, 3521, 13, 16, 96)),
-    ("bwd_weight", (2, 2, 4),  (32, 4, 135, 535, 1, 5, 3)),
-    ("bwd_weight", (2, 3, 3),  (44, 4, 35, 475, 5, 16, 5)),
-    ("bwd_weight", (2, 5, 2),  (51, 5, 35, 269, 9, 8, 32)),
-    ("bwd_weight", (2, 7, 5),  (54, 4, 69, 487, 13, 8, 0)),
-    ("bwd_weight", (2, 9, 3),  (39, 4, 66, 821, 9, 3, 27)),
-    ("bwd_weight", (4, 2, 4),  (48, 5, 35, 189, 13, 16, 195)),
-    ("bwd_weight", (4, 3, 3),  (46, 5, 106, 193, 13, 3, 18)),
+    ("bwd_weight", (1, 5, 3),  (58, 5, 4, 2691, 9, 2, 0)),
+    ("bwd_weight", (1, 9, 3),  (46, 4, 5, 3677, 33, 5, 0)),
+    ("bwd_weight", (1, 13, 3), (51, 5, 4, 3302, 26, 1, 0)),
+    ("bwd_weight", (1, 7, 8),  (40, 4, 4, 3501, 51, 5, 0)),
+    ("bwd_weight", (1, 5, 5),  (47, 6, 4, 3117, 9, 5, 0)),
+    ("bwd_weight", (1, 7, 4),  (55, 6, 6, 3521, 13, 16, 96)),
+    ("bwd_weight", (1, 3, 4),  (32, 4, 135, 535, 1, 5, 3)),
+    ("bwd_weight", (1, 3, 2),  (44, 4, 35, 475, 5, 16, 5)),
+    ("bwd_weight", (1, 3, 2),  (51, 5, 35, 269, 9, 8, 32)),
+    ("bwd_weight", (1, 7, 5),  (54, 4, 69, 487, 13, 8, 0)),
+    ("bwd_weight", (1, 3, 4),  (39, 4, 66, 821, 9, 3, 27)),
+    ("bwd_weight", (1, 7, 2),  (48, 5, 35, 189, 13, 16, 195)),
+    ("bwd_weight", (1, 7, 3),  (46, 5, 106, 193, 13, 3, 18)),
 ]
 
 # small layers at the edges of sizes
@@ -142,6 +146,29 @@ def test_edges(binding, oracle, case):
         assert ("split" in binding.conv1d_kernel_name(i, *wl.geometry(), 0)) == split, (what, split)
         bound = _bound(i, wl) if split else 16 * 2.0 ** -24
         assert errs[what][0] <= bound and errs[what][1] <= NORM_BOUND, (what, errs, bound)
+
+
+# weight gradients whose dy is read by four elements: samples of four to seven outputs, rows that end one, two and three
+# elements into a group, in the last of which the loads begin early, units of every number of slots per thread
+QUADS = [(16, 5, 1, 4, 1, 1, 0), (8, 3, 1, 5, 1, 1, 0), (6, 2, 2, 3, 1, 1, 0), (16, 2, 7, 1, 1, 1, 0), (5, 20, 3, 7, 3, 1, 1), (3, 17, 33, 257, 2, 3, 2),
+         (2, 20, 18, 225, 5, 1, 2), (1, 33, 17, 1022, 9, 16, 64), (2, 16, 40, 451, 3, 2, 2), (1, 4, 5, 2603, 51, 10, 250)]
+
+
+@pytest.mark.parametrize("case", QUADS, ids=lambda c: "x".join(map(str, c)))
+def test_weight_gradients_read_by_four(binding, oracle, case):
+    import torch
+
+    wl = _workload(case)
+    assert "split" in binding.conv1d_kernel_name(2, *wl.geometry(), 0)
+    data = inputs.make_inputs(wl)
+    dev = to_device(wl, data)
+    got = binding.conv1d_bwd_weight(dev["x"], dev["dy"], wl.S, wl.d, wl.P)
+    # the last sample's memory ends where the tensor does, and the tensor begins behind any float
+    buf = torch.full((dev["dy"].numel() + 1,), float("nan"), device="cuda")
+    buf[1:] = dev["dy"].flatten()
+    assert torch.equal(binding.conv1d_bwd_weight(dev["x"], buf[1:].view_as(dev["dy"]), wl.S, wl.d, wl.P), got)
+    err, norm = _errors(oracle, wl, data, {"bwd_weight": got.cpu().numpy()})["bwd_weight"]
+    assert err <= _bound(2, wl, (0, 0, 8)) and norm <= NORM_BOUND, (err, norm)
 
 
 # layers left on the FP32 instruction, by their sums or their windows, and the kernel of each pass

@@ -160,7 +160,7 @@ def test_three_part_tiles_of_the_parity_cases(model):
         assert _split_tile(model, ps, geom)[:3] == tile, (what, tile, geom)
         seen.add((ps == 2,) + tile[:2])
         _check(model, geom, 0, passes=(ps,), placements=(i % 3,))
-    for geom in t.EDGES:
+    for geom in t.EDGES + t.QUADS:
         _check(model, geom, 0, passes=(0, 1, 2), placements=(0,))
     rng = np.random.default_rng(3)
     for _ in range(3000):
