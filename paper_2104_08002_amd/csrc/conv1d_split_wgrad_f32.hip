@@ -7,7 +7,8 @@
 // 16 filters, 16 channels and TW NTW taps.  Eight of its waves multiply: wave v owns NTW of the taps and every WK-th
 // k-step of 32 positions (TW WK = 8), and the WK sums of a tap are added in a fixed order.  The other eight load, split and
 // write the next unit meanwhile (two units in LDS, the loads of two more in registers).
-// Partial tiles and second stage are those of the small-channel kernel, ws[(pair * strips + strip) * S + s][16][16].
+// Partial tiles and second stage are those of the small-channel kernel, ws[(pair * strips + strip) * S + s][16][16]; a layer
+// of one strip (few positions, or 129 block pairs and more) has neither.
 //
 // With many taps the matrix instructions bound it, at the clock they are granted with values as dense as these (C = K = 64,
 // S = 33: 1.25 of the 1.33 PFLOP/s that a large product of matrices reaches on such values); with few the loads and the
@@ -33,9 +34,10 @@ constexpr bool four_steps(int ntw) { return ntw <= 9 && ntw != 7; }  // dy of fo
 struct SwfArgs {
     const float* x;
     const float* dy;
-    float* ws;
+    float* ws;  // nullptr: one strip, straight into dw
+    float* dw;
     int C, K, W, Q, S, d, P;
-    long x_sn, dy_sn;
+    long x_sn, dy_sn, dw_sk, dw_sc;
     int N, qc, upr, nunits, strips, tw_sh, tgroups, kblocks, cblocks, lx, lxp;
 };
 
@@ -303,12 +305,16 @@ __global__ __launch_bounds__(2 * kRole, 4) void split_wgrad_f32_kernel(SwfArgs a
     if (wk != 0) return;
     const float turn = (u_begin & 1) ? -1.f : 1.f;  // such a strip added up its units with the opposite sign
     float* ws = a.ws + (static_cast<long>(kb * a.cblocks + cb) * a.strips + strip) * a.S * 256;
+    float* dw = a.dw + (k0 + 4 * g) * a.dw_sk + (c0 + l16) * a.dw_sc;
 #pragma unroll
     for (int i = 0; i < NTW; ++i) {
         const int s = s0 + tw * NTW + i;
         if (s < a.S)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) ws[s * 256 + (4 * g + j) * 16 + l16] = turn * acc[i][j];
+            for (int j = 0; j < 4; ++j) {
+                if (a.ws) ws[s * 256 + (4 * g + j) * 16 + l16] = turn * acc[i][j];
+                else if (k0 + 4 * g + j < a.K && c0 + l16 < a.C) dw[j * a.dw_sk + s] = turn * acc[i][j];
+            }
     }
 }
 
@@ -321,6 +327,10 @@ struct Plan {
 
 // positions of a plane of 8 channels, rounded up so that the two planes of a read begin in different halves of the banks
 long padded(long lx) { return ((lx + 7) & ~15L) + 8; }
+
+// N = 2, C = K = 4, W = 256, S = 5, d = 2, two units: 10.1 us in two strips, 9.3 in one; three units (N = 3,
+// C = K = 16, W = 256, S = 9): 10.0 in three strips, 10.8 in one.
+constexpr long kOneStrip = 2;
 
 // taps of a wave, within the 128 registers of 16 waves
 constexpr int kTaps[] = {3, 5, 7, 9, 13};
@@ -361,6 +371,8 @@ Plan make_plan(const WgradProblem& p) {
                 const long turn = per_strip < 256 ? 256 / per_strip : 1;
                 long strips = most < turn ? most : turn;
                 if (strips > nunits) strips = nunits;
+                // one strip while a few units cost less than the second stage, which it does without
+                if (nunits <= kOneStrip) strips = 1;
                 if (nunits > 0x3fffffffL || strips < 1 || strips * per_strip > (1 << 20)) continue;
                 const double longest = static_cast<double>((nunits + strips - 1) / strips);  // units of the longest strip
                 // Cycles of a unit on one SIMD, the products of its two multiplying waves beside what its two staging waves
@@ -369,7 +381,7 @@ Plan make_plan(const WgradProblem& p) {
                 const double mm = steps * (270.0 * ntw + 200.0), staging = 950.0 * (1 + cdiv(2 * lx, kRole));
                 const double unit = mm > staging ? mm + 0.26 * staging : staging + 0.26 * mm;
                 const double waves = static_cast<double>((strips * per_strip + 255) / 256);
-                const double cost = waves * (unit * longest + 11000 + WK * taps * 42.0);
+                const double cost = waves * (unit * longest + 11000 + WK * taps * 42.0) + (strips > 1 ? 7000 : 0);
                 if (best.ok && cost >= best_cost) continue;
                 best_cost = cost;
                 best.ok = true;
@@ -386,7 +398,8 @@ Plan make_plan(const WgradProblem& p) {
     SwfArgs& a = best.a;
     a.x = static_cast<const float*>(p.x);
     a.dy = static_cast<const float*>(p.dy);
-    a.ws = static_cast<float*>(p.ws);
+    a.ws = a.strips > 1 ? static_cast<float*>(p.ws) : nullptr;
+    a.dw = p.dw; a.dw_sk = p.dw_sk; a.dw_sc = p.dw_sc;
     a.N = p.N; a.C = p.C; a.K = p.K; a.W = p.W; a.Q = p.Q; a.S = p.S; a.d = p.d; a.P = p.P;
     a.x_sn = p.x_sn; a.dy_sn = p.dy_sn;
     a.cblocks = cblocks; a.kblocks = kblocks;
@@ -425,7 +438,7 @@ hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* t
         case 13: e = run<13>(pl, st); break;
         default: return hipErrorInvalidValue;
     }
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || pl.a.strips == 1) return e;
     return smallc_wgrad_reduce_launch(pl.a.ws, p.dw, p.K, p.C, p.S, p.dw_sk, p.dw_sc, pl.a.strips, st);
 }
 
