@@ -36,18 +36,16 @@ class Conv1dFunction(torch.autograd.Function):
     def backward(ctx, gy):
         x, w = ctx.saved_tensors
         d, P = ctx.geometry
-        bf16 = x.dtype == torch.bfloat16
-        if torch.is_grad_enabled() and gy.requires_grad:   # create_graph: the bias gradient is differentiable in gy
+        positive = ctx.y_positive if ctx.relu else None
+        if gy.requires_grad and torch.is_grad_enabled():   # create_graph: the bias gradient is differentiable in gy
             dy = gy
-            if ctx.relu:
+            if positive is not None:
                 bit = torch.arange(8, dtype=torch.uint8, device=gy.device)
-                dy = gy * ((ctx.y_positive[:, None] >> bit) & 1).bool().flatten()[:gy.numel()].view(gy.shape)
+                dy = gy * ((positive[:, None] >> bit) & 1).bool().flatten()[:gy.numel()].view(gy.shape)
             gb = dy.float().sum(dim=(0, 2)) if ctx.has_bias else None
-            dy = dy.to(x.dtype).contiguous()
+            dx, dw = binding.conv1d_bwd_ex(x, dy.to(x.dtype).contiguous(), w, d, P, out_bf16=x.dtype == torch.bfloat16)
         else:
-            dy, gb = binding.conv1d_epilogue_bwd(gy.resolve_neg().contiguous(), ctx.y_positive if ctx.relu else None, x.dtype,
-                                                 ctx.has_bias)
-        dx, dw = binding.conv1d_bwd_ex(x, dy, w, d, P, out_bf16=bf16)
+            dx, dw, gb = binding.conv1d_layer_bwd(gy.resolve_neg().contiguous(), positive, x, w, d, P, ctx.has_bias)
         return dx, dw.to(w.dtype), gb, None, None, None, None
 
 
