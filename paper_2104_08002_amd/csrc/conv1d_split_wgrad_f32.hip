@@ -367,9 +367,15 @@ Plan make_plan(const WgradProblem& p) {
                 if (steps == 1 && !two_sums(ntw) && QC < kMaxUnit && QC < p.Q) continue;
                 const int upr = cdiv(p.Q, QC);
                 const long nunits = static_cast<long>(p.N) * upr;
-                // no more workgroups than CUs (six pairs of blocks in 43 strips each took two turns: 34 instead of 26 us)
-                const long turn = per_strip < 256 ? 256 / per_strip : 1;
-                long strips = most < turn ? most : turn;
+                // As many strips as the workspace holds, but no few workgroups over a whole number per CU: six pairs of
+                // blocks in 43 strips took two turns, 34 us, where 42 strips take 26.  One turn at most where the k-steps
+                // that are summed by themselves more than make up for the longer sums of fewer strips (with as many: N = 53,
+                // C = 40, K = 7, W = 9177, S = 51, d = 16 1.8e-7 off where 1.6e-7 in all strips).
+                const long turns = (most * per_strip + 255) / 256, one = per_strip < 256 ? 256 / per_strip : 1;
+                const long by_itself = (steps < 2 ? 1 : steps >= 4 && four_steps(ntw) ? 4 : 2) * (two_sums(ntw) ? 2 : 1);
+                long strips = most;
+                if (turns > 1 && one * by_itself >= 2 * most) strips = one;
+                else if (turns > 1 && most * per_strip < turns * 230 && 256 * (turns - 1) >= per_strip) strips = 256 * (turns - 1) / per_strip;
                 if (strips > nunits) strips = nunits;
                 // one strip while a few units cost less than the second stage, which it does without
                 if (nunits <= kOneStrip) strips = 1;
