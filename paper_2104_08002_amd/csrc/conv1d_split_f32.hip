@@ -236,7 +236,8 @@ struct Plan {
 struct Fit {
     bool ok;
     int nsteps, nstages, resident;
-    long wlen, per_sample;  // workgroups of a sample
+    long columns, wlen;  // columns of a window, and slots of a plane of it
+    long per_sample;     // workgroups of a sample
     size_t lds;
     double alone, busy;
     double time(long grid) const {
@@ -251,6 +252,8 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
     f.nsteps = cdiv(p.S, tp);
     f.nstages = cdiv(p.R, 8 << sh);
     f.wlen = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
+    f.columns = f.wlen;
+    if (sh > 0) f.wlen = (f.wlen + 15) & ~15L;  // the planes of a read begin in the same bank (C = K = 48, S = 17, d = 3: 40.0 -> 38.8 us)
     f.lds = (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16;
     if (f.wlen > 16384 || f.lds > kLdsAll) return f;
     const long columns = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * 64 * t.pb;  // the last tile may end behind the row
@@ -259,7 +262,7 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
     f.resident = by_lds < by_regs ? by_lds : by_regs;
     if (f.resident < 1) f.resident = 1;
     f.per_sample = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * cdiv(cdiv(p.M, 16), t.fbw);
-    const double window = static_cast<double>(f.wlen << sh);
+    const double window = static_cast<double>(f.columns << sh);
     const double mm = 150.0 * t.fbw * t.pb, loads = 610.0 * t.fbw + 31.0 * (t.fbw + t.pb);
     f.alone = f.nstages * (f.nsteps * (240.0 + 350.0 * t.fbw + (22.0 + 100.0 * t.fbw) * t.pb + (t.fbw > 2 ? 1000.0 : 0.0)) + 6 * window);
     f.busy = f.nstages * (f.nsteps * (mm > loads ? mm : loads) + 3.6 * window);
@@ -270,7 +273,17 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
 // Planes per step (1 << result), which decides the order of an output's sum: from what a sample is, not from how many there
 // are, so that a sample's result does not depend on its batch.  The least of matrix time plus what steps and windows cost
 // beside it over the tiles of 256 columns and more; workgroups that share a CU hide half of the latter.  -1: none fits.
+// Long rows of many filters and taps take one plane, four taps a step: the windows are short beside the steps then, and their
+// workgroups share CUs three at a time.  S = 51, d = 1, W = 60000, one plane and two: N = 1, C = K = 64 136 and 139 us, 128 473
+// and 499, 256 1772 and 1948; shorter rows lose with one where the batch is small (N = 1, W = 20000, C = K = 64: 83.7 and 81.5)
+// and gain where it is not (N = 4: 172 and 178).
+constexpr int kLongTaps = 40;
+constexpr long kLongRows = 2400000;  // filters x columns of a sample
+
 int planes_shift(const CorrProblem& p) {
+    if (p.S >= kLongTaps && static_cast<long>(p.M) * p.Wout >= kLongRows)
+        for (const Tile t : kTiles)
+            if (t.pb >= 4 && 16 * (t.fbw - 1) < p.M && fit(p, t, 0).ok) return 0;
     int best = -1;
     double best_cost = 0;
     for (const Tile t : kTiles) {
@@ -278,8 +291,9 @@ int planes_shift(const CorrProblem& p) {
         for (int sh = 0; sh <= 2; ++sh) {
             const Fit f = fit(p, t, sh);
             if (!f.ok) continue;
-            const double beside = f.nsteps * 600.0 + 1000.0 + (f.wlen << sh) * 2.0;
-            const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * f.lds <= kLdsAll ? 0.5 : 1.0) * beside);
+            const size_t bare = f.lds - static_cast<size_t>(f.wlen - f.columns) * 48 * (1 << sh);
+            const double beside = f.nsteps * 600.0 + 1000.0 + (f.columns << sh) * 2.0;
+            const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * bare <= kLdsAll ? 0.5 : 1.0) * beside);
             if (best >= 0 && cost >= best_cost) continue;
             best_cost = cost;
             best = sh;
