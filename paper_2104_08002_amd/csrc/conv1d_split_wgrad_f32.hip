@@ -290,16 +290,17 @@ __global__ __launch_bounds__(2 * kRole, 4) void split_wgrad_f32_kernel(SwfArgs a
 #pragma unroll
     for (int i = 0; i < NTW; ++i) acc[i] = NS == 2 ? sums[0][i] - sums[NS - 1][i] : sums[0][i];
 
-    // the k-step shares of a tap, left to right
+    // the k-step shares of a tap, the upper half of them to the lower (one after the other: 0.4 us more for the eight of S = 5)
     f32x4* red = reinterpret_cast<f32x4*>(lds);
-    for (int r = 1; r < WK; ++r) {
-        if (wk == r)
+    for (int half = WK / 2; half > 0; half /= 2) {
+        f32x4* mine = red + ((wk & (half - 1)) * TW + tw) * NTW * 64 + lane;
+        if (wk >= half && wk < 2 * half)
 #pragma unroll
-            for (int i = 0; i < NTW; ++i) red[(tw * NTW + i) * 64 + lane] = acc[i];
+            for (int i = 0; i < NTW; ++i) mine[i * 64] = acc[i];
         __syncthreads();
-        if (wk == 0)
+        if (wk < half)
 #pragma unroll
-            for (int i = 0; i < NTW; ++i) acc[i] += red[(tw * NTW + i) * 64 + lane];
+            for (int i = 0; i < NTW; ++i) acc[i] += mine[i * 64];
         __syncthreads();
     }
     if (wk != 0) return;
@@ -359,7 +360,7 @@ Plan make_plan(const WgradProblem& p) {
                 if (QC < 32) continue;
                 const long lx = QC + halo, lxp = padded(lx);
                 const size_t stage = static_cast<size_t>(3 * (2 * QC + 2 * lxp)) * 16;
-                const size_t red = WK > 1 ? static_cast<size_t>(taps) * 1024 : 0;
+                const size_t red = WK > 1 ? static_cast<size_t>(taps) * (WK / 2) * 1024 : 0;
                 const size_t lds = red > 2 * stage ? red : 2 * stage;
                 if (2 * lx > kXTasks * kRole || lds > kLdsAll) continue;
                 const int steps = cdiv(QC / 32, WK);
