@@ -427,6 +427,7 @@ hipError_t run(const Plan& pl, hipStream_t st) {
 bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; }
 
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
+    if (make_plan(p).ok && split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_tile(p, t);
     const Plan pl = make_plan(p);
     *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
     return pl.ok;
@@ -436,6 +437,7 @@ hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* t
     const Plan pl = make_plan(p);
     *taken = pl.ok;
     if (!pl.ok) return hipSuccess;
+    if (split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_launch(p, st);
     hipError_t e;
     switch (pl.ntw) {
         case 3: e = run<3>(pl, st); break;

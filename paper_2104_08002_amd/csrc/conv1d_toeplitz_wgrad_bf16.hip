@@ -13,7 +13,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Adds the strips in a fixed order (16 interleaved running sums per element, then those 16 in order) and
 // scatters the tiles into dw[k][c][s].  A block of 16 x 16 threads handles 64 consecutive tile elements: thread
-// (g, el) adds the strips g, g + 16, ... of the 4 elements 4 el .. 4 el + 3 with 16-byte loads, eight of them in flight
+// (g, el) adds the strips g, g + 16, ... of the 4 elements 4 el .. 4 el + 3 with 16-byte loads, four of them in flight
 // (280 strips of C = K = 16, S = 51: 8.6 us one by one, now 5.3).  The tile size is a multiple of 256, so a block never
 // straddles two combinations.
 __global__ __launch_bounds__(256) void toeplitz_wgrad_reduce_kernel(const float* __restrict__ ws, float* __restrict__ dw, TzArgs a, int FB, int NTW) {
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void toeplitz_wgrad_reduce_kernel(const float*
     const int combo = static_cast<int>(idx / tile), e = static_cast<int>(idx - static_cast<long>(combo) * tile);
     f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
     if (combo < ncombos)
-#pragma unroll 8
+#pragma unroll 4
         for (int s = g; s < a.nstrips; s += 16) sum += *reinterpret_cast<const f32x4*>(ws + (static_cast<long>(s) * ncombos + combo) * tile + e);
     part[g][el] = sum;
     __syncthreads();

@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
 PASSES = ("fwd", "bwd_data", "bwd_weight")
 
 # pass, tile, N  C  K  W  S  d  P.  tile: filter blocks of 16 and column blocks of 64 of a workgroup, planes of 8 channels of
-# a step; for the weight gradient one filter block, taps of a wave, units of the longest strip (the CPU test of the library's
+# a step; for the weight gradient filter blocks, taps of a wave, units of the longest strip (the CPU test of the library's
 # bounds model checks that these are the tiles taken).  Widths of the output are odd and end inside a tile, filters end
 # inside a block, and groups of filter blocks lack one.
 TILES = [
@@ -61,6 +61,13 @@ TILES = [
     ("bwd_weight", (1, 3, 4),  (39, 4, 66, 821, 9, 3, 27)),
     ("bwd_weight", (1, 7, 2),  (48, 5, 35, 189, 13, 16, 195)),
     ("bwd_weight", (1, 7, 3),  (46, 5, 106, 193, 13, 3, 18)),
+    ("bwd_weight", (2, 2, 3),  (5, 202, 163, 21, 6, 3, 0)),
+    ("bwd_weight", (2, 3, 6),  (11, 132, 269, 318, 22, 15, 0)),
+    ("bwd_weight", (2, 5, 14), (27, 170, 233, 353, 33, 11, 0)),
+    ("bwd_weight", (2, 7, 1),  (2, 274, 203, 140, 44, 2, 0)),
+    ("bwd_weight", (2, 9, 6),  (4, 132, 282, 399, 35, 7, 0)),
+    ("bwd_weight", (4, 2, 1),  (2, 204, 184, 45, 27, 1, 0)),
+    ("bwd_weight", (4, 3, 1),  (2, 133, 240, 222, 52, 4, 0)),
 ]
 
 # small layers at the edges of sizes
