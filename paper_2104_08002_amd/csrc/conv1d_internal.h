@@ -152,10 +152,12 @@ hipError_t igemm_stream_bf16_corr_launch(const CorrProblem& p, hipStream_t st);
 bool split_f32_corr_supported(const CorrProblem& p);
 hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st, bool* taken);
 // what such a launch would take (the tests choose their geometries by it): filter blocks of 16 per workgroup; column blocks
-// of 64 per workgroup, or taps per wave; planes of 8 channels per step, or units of the longest strip; workgroups
+// of 64 per workgroup, or taps per wave; planes of 8 channels per step, or units of the longest strip; workgroups; for the
+// weight gradient the roundings of its sums (chain_roundings) before the second stage
 struct SplitTile {
     int filter_blocks, columns_or_taps, planes_or_units;
     long grid;
+    double roundings;
 };
 bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t);
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
@@ -164,6 +166,8 @@ bool split_f32_wgrad_supported(const WgradProblem& p);
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken);
 // the same with two blocks of filters per workgroup, which that launch leaves some layers to
 bool split_f32_wgrad_pair_taken(const WgradProblem& p);
+// roundings of a sum in the tile it would take, whether it is left the layer or not, before the second stage; 0: takes none
+double split_f32_wgrad_pair_roundings(const WgradProblem& p);
 bool split_f32_wgrad_pair_tile(const WgradProblem& p, SplitTile* t);
 hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st);
 

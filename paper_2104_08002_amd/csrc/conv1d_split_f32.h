@@ -67,5 +67,9 @@ constexpr long kMinTerms = 16;
 // v_mfma_f32_16x16x4_f32.
 constexpr int kPartA[6] = {2, 0, 1, 1, 0, 0}, kPartB[6] = {0, 2, 1, 0, 1, 0};
 
+// What a chain of n additions of independent terms rounds off, in roundings of the whole sum: partial sums grow as the
+// root of their number, so their squares add up to this many of the last one's.
+inline double chain_roundings(long n) { return n > 1 ? 0.5 * static_cast<double>(n + 1) - 1.0 / static_cast<double>(n) : 0.0; }
+
 }  // namespace sp
 }  // namespace conv1d

@@ -324,6 +324,7 @@ struct Plan {
     int ntw, grid;
     SwfArgs a;
     size_t lds;
+    double roundings;
 };
 
 // positions of a plane of 8 channels, rounded up so that the two planes of a read begin in different halves of the banks
@@ -336,7 +337,17 @@ constexpr long kOneStrip = 2;
 // taps of a wave, within the 128 registers of 16 waves
 constexpr int kTaps[] = {3, 5, 7, 9, 13};
 
-Plan make_plan(const WgradProblem& p) {
+// Roundings of a weight gradient before its second stage: a strip of `longest` units of `steps` k-steps per wave, then the
+// WK shares of a tap as a tree and, where every other unit has a sum of its own, the difference of the two.
+double roundings(int ntw, int WK, int steps, long longest) {
+    const int left = four_steps(ntw) ? steps % 4 : steps, adds = (steps - left) / 4 + left / 2 + left % 2;
+    double r = chain_roundings(adds * (two_sums(ntw) ? (longest + 1) / 2 : longest)) + (two_sums(ntw) && longest > 1 ? 1 : 0);
+    for (; WK > 1; WK /= 2) r += 1;
+    return r;
+}
+
+// the fastest tile of at most so many roundings
+Plan search(const WgradProblem& p, double most_roundings) {
     Plan best{};
     if (p.bf16 || p.dw_sc != p.S || static_cast<long>(p.N) * p.Q < kMinTerms) return best;
     if (static_cast<long>(p.K) * p.Q < 4) return best;  // dy is loaded by four elements of a sample
@@ -380,8 +391,12 @@ Plan make_plan(const WgradProblem& p) {
                 if (strips > nunits) strips = nunits;
                 // one strip while a few units cost less than the second stage, which it does without
                 if (nunits <= kOneStrip) strips = 1;
+                const long all = most < nunits ? most : nunits;
+                if (strips > 0 && roundings(ntw, WK, steps, (nunits + strips - 1) / strips) > most_roundings) strips = all;
                 if (nunits > 0x3fffffffL || strips < 1 || strips * per_strip > (1 << 20)) continue;
-                const double longest = static_cast<double>((nunits + strips - 1) / strips);  // units of the longest strip
+                const long longest = (nunits + strips - 1) / strips;  // units of the longest strip
+                const double rounded = roundings(ntw, WK, steps, longest);
+                if (rounded > most_roundings) continue;
                 // Cycles of a unit on one SIMD, the products of its two multiplying waves beside what its two staging waves
                 // do; a fit to all tiles on 17 layers (C, K 4 ... 256, 1 ... 51 taps): what is taken is within 9 % of the
                 // fastest, 2 % on average.
@@ -394,6 +409,7 @@ Plan make_plan(const WgradProblem& p) {
                 best.ok = true;
                 best.ntw = ntw;
                 best.lds = lds;
+                best.roundings = rounded;
                 best.grid = static_cast<int>(strips * per_strip);
                 SwfArgs& a = best.a;
                 a.qc = static_cast<int>(QC); a.upr = upr; a.nunits = static_cast<int>(nunits); a.strips = static_cast<int>(strips);
@@ -413,6 +429,25 @@ Plan make_plan(const WgradProblem& p) {
     return best;
 }
 
+// The fastest tile may keep fewer sums than the kernel of several filter blocks, which takes all strips and mostly eight
+// shares: no tile rounds more often than that kernel would.  Error against 64 bits in 1e-7, time in us, of the fastest tile,
+// of this rule and of that kernel: N = 33, C = K = 160, W = 957, S = 33, d = 12 2.3, 1.4 and 1.4, 326, 388 and 727; N = 8,
+// C = 144, K = 160, W = 11290, S = 25, d = 4 2.5, 2.0 and 2.1, 635, 842 and 1319; N = 41, C = 42, K = 40, W = 55280, S = 46,
+// d = 16 3.4, 2.6 and 3.4, 3120, 3060 and 4280.  One layer in 25 takes another tile for it.  A few roundings are less than
+// those of the steps and of the second stage, and are not compared (a second search, 2 us of host time, would show in the
+// short launches that have so few).
+constexpr double kFewRoundings = 8;
+
+Plan make_plan(const WgradProblem& p) {
+    const Plan fastest = search(p, 1e300);
+    if (!fastest.ok || fastest.roundings <= kFewRoundings) return fastest;
+    double most = split_f32_wgrad_pair_roundings(p);
+    if (most < kFewRoundings) most = kFewRoundings;
+    if (fastest.roundings <= most) return fastest;
+    const Plan fewer = search(p, most);
+    return fewer.ok ? fewer : fastest;  // (no layer of 50000 of all kinds was without one)
+}
+
 template <int NTW>
 hipError_t run(const Plan& pl, hipStream_t st) {
     const int xt = cdiv(pl.a.lx, kRole / 2);
@@ -429,7 +464,7 @@ bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; 
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
     if (make_plan(p).ok && split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_tile(p, t);
     const Plan pl = make_plan(p);
-    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
+    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, pl.roundings};
     return pl.ok;
 }
 

@@ -369,9 +369,16 @@ bool split_f32_wgrad_pair_taken(const WgradProblem& p) {
     return (idle || halo) && make_plan(p).ok;
 }
 
+double split_f32_wgrad_pair_roundings(const WgradProblem& p) {
+    const Plan pl = make_plan(p);
+    if (!pl.ok) return 0.0;
+    const int WK = 8 >> pl.a.tw_sh;
+    return chain_roundings(static_cast<long>((1 << pl.a.qc_sh) / 32 / WK) * cdiv(pl.a.nunits, pl.a.strips)) + chain_roundings(WK);
+}
+
 bool split_f32_wgrad_pair_tile(const WgradProblem& p, SplitTile* t) {
     const Plan pl = make_plan(p);
-    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid};
+    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, split_f32_wgrad_pair_roundings(p)};
     return pl.ok;
 }
 

@@ -200,6 +200,16 @@ extern "C" int hostmodel_split_tile(int pass, int N, int C, int K, int W, int S,
     return ok;
 }
 
+// Roundings of a weight gradient's sums in the tile taken (0: none is) and in that of the kernel of several filter blocks.
+extern "C" void hostmodel_wgrad_roundings(int N, int C, int K, int W, int S, int d, int P, double* r) {
+    conv1d::WgradProblem p{};
+    p.N = N; p.C = C; p.K = K; p.W = W; p.Q = W + 2 * P - (S - 1) * d; p.S = S; p.d = d; p.P = P;
+    p.x_sn = static_cast<long>(C) * W; p.dy_sn = static_cast<long>(K) * p.Q; p.dw_sk = static_cast<long>(C) * S; p.dw_sc = S;
+    conv1d::SplitTile t{};
+    r[0] = conv1d::split_f32_wgrad_tile(p, &t) ? t.roundings : 0.0;
+    r[1] = conv1d::split_f32_wgrad_pair_roundings(p);
+}
+
 // The multiply-high division of the kernels against the plain one: the first n <= nmax whose quotient differs, -1 if
 // none does, -2 if make_fastdiv refuses the pair (it must refuse every pair for which the quotient could be wrong).
 extern "C" long hostmodel_fastdiv_mismatch(long d, long nmax) {

@@ -178,6 +178,28 @@ def test_weight_gradients_read_by_four(binding, oracle, case):
     assert err <= _bound(2, wl, (0, 0, 8)) and norm <= NORM_BOUND, (err, norm)
 
 
+# layers whose fastest tile has half the running sums, and the roundings of their sums in all strips: 2.3e-7 and 2.3e-7 so
+MANY_ROUNDINGS = [((33, 160, 160, 957, 33, 12, 192), 28.6), ((2, 133, 133, 28080, 33, 10, 160), 34.6)]
+
+
+@pytest.mark.parametrize("case", MANY_ROUNDINGS, ids=lambda c: "x".join(map(str, c[0])))
+def test_weight_gradients_keep_their_roundings(binding, case):
+    """n independent roundings of up to 2^-24 / sqrt(3) of the sum (root mean square), which is the norm of the error."""
+    import torch
+
+    (N, C, K, W, S, d, P), n = case
+    gen = torch.Generator(device="cuda").manual_seed(23)
+    Q = W + 2 * P - (S - 1) * d
+    x = torch.rand((N, C, W), generator=gen, device="cuda") * 2 - 1
+    dy = torch.rand((N, K, Q), generator=gen, device="cuda") * 2 - 1
+    dw = binding.conv1d_bwd_weight(x, dy, S, d, P).double()
+    xp, gt = torch.nn.functional.pad(x.double(), (P, P)), dy.double().transpose(1, 2).contiguous()
+    ref = torch.stack([torch.matmul(xp[:, :, t * d:t * d + Q].contiguous(), gt).sum(0).t() for t in range(S)], 2)
+    norm = float((dw - ref).norm() / ref.norm())
+    print(case, norm, flush=True)
+    assert norm <= 2.0 ** -24 * (n / 3) ** 0.5, norm
+
+
 # layers left on the FP32 instruction, by their sums or their windows, and the kernel of each pass
 LEFT = [
     # N  C   K   W     S  d     P      forward, backward-data, backward-weight

@@ -172,6 +172,29 @@ def test_three_part_tiles_of_the_parity_cases(model):
                 assert tile is None or (ps == 2,) + tile[:2] in seen, (ps, geom, tile)
 
 
+def _roundings(lib, geom):
+    r = (ctypes.c_double * 2)()
+    lib.hostmodel_wgrad_roundings(*geom, r)
+    return r[0], r[1]
+
+
+def test_fp32_weight_gradients_round_no_more_often_than_in_all_strips(model):
+    """The tiles of the kernel with waves for staging and multiplying may be shorter of sums than those of the kernel of
+    several filter blocks (all strips, eight shares of most taps), never with more roundings, but for a handful."""
+    for geom, most in [((33, 160, 160, 957, 33, 12, 192), 27), ((2, 133, 133, 28080, 33, 10, 160), 33), ((16, 15, 15, 60000, 51, 8, 200), 32)]:
+        assert 0 < _roundings(model, geom)[0] <= most, (geom, _roundings(model, geom))
+    rng = np.random.default_rng(17)
+    seen = 0
+    for _ in range(4000):
+        geom = tuple(int(v) for v in (np.exp(rng.uniform(0, 4.1)), np.exp(rng.uniform(0, 5.7)), np.exp(rng.uniform(0, 5.7)),
+                                      np.exp(rng.uniform(5, 11)), rng.integers(1, 53), rng.integers(1, 17), 0))
+        if geom[3] > (geom[4] - 1) * geom[5]:
+            taken, other = _roundings(model, geom)
+            assert taken <= max(other, 8) + 1e-6, (geom, taken, other)
+            seen += taken > 8
+    assert seen > 300
+
+
 def test_launches_of_fp32_layers_off_the_three_part_kernels(model):
     """What the three-part kernels leave still runs as before: one launch while the weights of all channel blocks and the
     window fit in LDS, else one per channel block, with bias and ReLU in a launch of their own at the end."""
