@@ -153,18 +153,20 @@ bool split_f32_corr_supported(const CorrProblem& p);
 hipError_t split_f32_corr_launch(const CorrProblem& p, hipStream_t st, bool* taken);
 // what such a launch would take (the tests choose their geometries by it): filter blocks of 16 per workgroup; column blocks
 // of 64 per workgroup, or taps per wave; planes of 8 channels per step, or units of the longest strip; workgroups; for the
-// weight gradient the roundings of its sums (chain_roundings) before the second stage
+// weight gradient the roundings of its sums (chain_roundings) before the second stage, and the slots of x of a staging thread
+// (0: the kernel of several filter blocks)
 struct SplitTile {
     int filter_blocks, columns_or_taps, planes_or_units;
     long grid;
     double roundings;
+    int x_slots;
 };
 bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t);
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
 // FP32 backward-weight the same way; workspace and second stage of smallc_wgrad_f32_blocks_*
 bool split_f32_wgrad_supported(const WgradProblem& p);
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken);
-// the same with two blocks of filters per workgroup, which that launch leaves some layers to
+// the same with two or four blocks of filters per workgroup, which that launch leaves some layers to
 bool split_f32_wgrad_pair_taken(const WgradProblem& p);
 // roundings of a sum in the tile it would take, whether it is left the layer or not, before the second stage; 0: takes none
 double split_f32_wgrad_pair_roundings(const WgradProblem& p);

@@ -363,7 +363,7 @@ bool split_f32_corr_supported(const CorrProblem& p) { return make_plan(p).ok; }
 
 bool split_f32_corr_tile(const CorrProblem& p, SplitTile* t) {
     const Plan pl = make_plan(p);
-    *t = SplitTile{pl.tile.fbw, pl.tile.pb, 1 << pl.a.pl_sh, pl.grid, 0.0};
+    *t = SplitTile{pl.tile.fbw, pl.tile.pb, 1 << pl.a.pl_sh, pl.grid, 0.0, 0};
     return pl.ok;
 }
 

@@ -464,7 +464,7 @@ bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; 
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
     if (make_plan(p).ok && split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_tile(p, t);
     const Plan pl = make_plan(p);
-    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, pl.roundings};
+    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, pl.roundings, cdiv(pl.a.lx, kRole / 2)};
     return pl.ok;
 }
 

@@ -1,4 +1,4 @@
-// FP32 backward-weight on the bf16 matrix instructions, one, two or four blocks of 16 filters per workgroup, in waves that
+// FP32 backward-weight on the bf16 matrix instructions, two or four blocks of 16 filters per workgroup, in waves that
 // split as well as multiply (see conv1d_split_wgrad_f32.hip for the kernel that has waves for each, the splitting and the
 // partial tiles).
 //
@@ -22,7 +22,7 @@ constexpr int kThreads = 512;
 constexpr size_t kLdsAll = 160 * 1024;
 // 16-byte slots of dy and x a thread stages per unit, and register sets
 constexpr int kDyTasks = 2, kXTasks = 3;
-constexpr int num_sets(int fbw, int ntw) { return (fbw == 1 && ntw <= 9) || fbw * ntw <= 6 ? 2 : 1; }
+constexpr int num_sets(int fbw, int ntw) { return fbw * ntw <= 6 ? 2 : 1; }
 
 struct SwfArgs {
     const float* x;
@@ -180,44 +180,33 @@ __global__ __launch_bounds__(kThreads, 2) void split_wgrad_pair_f32_kernel(SwfAr
             for (int f = 0; f < FBW; ++f)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) y[f][i] = dys[i * ndy + f * (QC * 2) + ks * 64];
-            // U taps at a time: the reads of the next ones are issued in front of the products of these, and no earlier
-            // (left to itself the compiler reads further ahead and spills)
-            constexpr int U = FBW == 1 ? 2 : 1;
-            u32x4 b[2][U][3];
+            // the reads of the next tap are issued in front of the products of this one, and no earlier (left to itself the
+            // compiler reads further ahead and spills)
+            u32x4 b[2][3];
             int at = xs0 + 128 * ks;
             auto read = [&](int t) {
 #pragma unroll
-                for (int v = 0; v < U; ++v)
-                    if (t + v < NTW) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            const u32x2* p = reinterpret_cast<const u32x2*>(lds) + at + i * 2 * nx;
-                            const u32x2 lo = read_tr(p), hi = read_tr(p + 64);
-                            b[(t / U) & 1][v][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                        }
-                        at += 4 * a.d;
-                        opaque(at);  // one running index, not one register per tap and part
-                    }
+                for (int i = 0; i < 3; ++i) {
+                    const u32x2* p = reinterpret_cast<const u32x2*>(lds) + at + i * 2 * nx;
+                    const u32x2 lo = read_tr(p), hi = read_tr(p + 64);
+                    b[t & 1][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                }
+                at += 4 * a.d;
+                opaque(at);  // one running index, not one register per tap and part
             };
             read(0);
 #pragma unroll
-            for (int t = 0; t < NTW; t += U) {
-                if (t + U < NTW) read(t + U);
+            for (int t = 0; t < NTW; ++t) {
+                if (t + 1 < NTW) read(t + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                f32x4 part[U][FBW];
+                f32x4 part[FBW];
 #pragma unroll
                 for (int k = 0; k < 6; ++k)
 #pragma unroll
-                    for (int v = 0; v < U; ++v)
-                        if (t + v < NTW)
+                    for (int f = 0; f < FBW; ++f)
+                        part[f] = mfma(y[f][kPartB[k]], b[t & 1][kPartA[k]], k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[f]);
 #pragma unroll
-                            for (int f = 0; f < FBW; ++f)
-                                part[v][f] = mfma(y[f][kPartB[k]], b[(t / U) & 1][v][kPartA[k]], k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[v][f]);
-#pragma unroll
-                for (int v = 0; v < U; ++v)
-                    if (t + v < NTW)
-#pragma unroll
-                        for (int f = 0; f < FBW; ++f) acc[t + v][f] = PAR ? acc[t + v][f] - part[v][f] : acc[t + v][f] + part[v][f];
+                for (int f = 0; f < FBW; ++f) acc[t][f] = PAR ? acc[t][f] - part[f] : acc[t][f] + part[f];
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -276,6 +265,8 @@ struct Plan {
     size_t lds;
 };
 
+// Filter blocks and taps of a wave.  Shapes of one block are priced, not run: where one of them would be the fastest, the
+// kernel that has waves for each is faster still (see split_f32_wgrad_pair_taken).
 constexpr int kShapes[][2] = {{1, 3}, {1, 5}, {1, 7}, {1, 9}, {1, 13}, {2, 2}, {2, 3}, {2, 5}, {2, 7}, {2, 9}, {4, 2}, {4, 3}};
 
 Plan make_plan(const WgradProblem& p) {
@@ -361,12 +352,17 @@ hipError_t run(const Plan& pl, hipStream_t st) {
 
 // Layers of 129 to 255 pairs of blocks, one workgroup of which would leave up to half of the CUs idle, and of many pairs with
 // a halo of 600 positions and more, over 60 layers drawn from 4 ... 256 channels and 5 ... 51 taps (fewer taps: N = 1, C = K =
-// 200, W = 2000, S = 3 22 us here, 17 in the other kernel).
+// 200, W = 2000, S = 3 22 us here, 17 in the other kernel).  Not where one block per workgroup is the best that can be done
+// here, one in thirty of them: x is split for that block alone then, and over 19 such layers the other kernel takes 0.47 to
+// 0.97 of the time (N = 5, C = K = 198, W = 6153, S = 49, d = 3 890 and 741 us; N = 1, C = K = 238, W = 232, S = 17, d = 4 29
+// and 14), in one 1.04 (N = 48, C = 210, K = 208, W = 2788, S = 39, d = 16 3170 and 3300), with smaller errors in all.
 bool split_f32_wgrad_pair_taken(const WgradProblem& p) {
     const long pairs = static_cast<long>(cdiv(p.C, 16)) * cdiv(p.K, 16);
     const bool idle = pairs > 128 && pairs < 256 && p.S >= 5;
     const bool halo = (p.S - 1L) * p.d >= 600 && pairs >= 48;
-    return (idle || halo) && make_plan(p).ok;
+    if (!idle && !halo) return false;
+    const Plan pl = make_plan(p);
+    return pl.ok && pl.fbw > 1;
 }
 
 double split_f32_wgrad_pair_roundings(const WgradProblem& p) {
@@ -378,7 +374,7 @@ double split_f32_wgrad_pair_roundings(const WgradProblem& p) {
 
 bool split_f32_wgrad_pair_tile(const WgradProblem& p, SplitTile* t) {
     const Plan pl = make_plan(p);
-    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, split_f32_wgrad_pair_roundings(p)};
+    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, split_f32_wgrad_pair_roundings(p), 0};
     return pl.ok;
 }
 
@@ -387,11 +383,6 @@ hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st) {
     if (!pl.ok) return hipErrorInvalidValue;
     hipError_t e;
     switch (pl.fbw * 16 + pl.ntw) {
-        case 16 + 3: e = run<1, 3>(pl, st); break;
-        case 16 + 5: e = run<1, 5>(pl, st); break;
-        case 16 + 7: e = run<1, 7>(pl, st); break;
-        case 16 + 9: e = run<1, 9>(pl, st); break;
-        case 16 + 13: e = run<1, 13>(pl, st); break;
         case 32 + 2: e = run<2, 2>(pl, st); break;
         case 32 + 3: e = run<2, 3>(pl, st); break;
         case 32 + 5: e = run<2, 5>(pl, st); break;

@@ -178,8 +178,8 @@ extern "C" const char* hostmodel_kernel_name(int pass, int N, int C, int K, int 
 
 extern "C" int hostmodel_launches() { return g_launches; }
 
-// Tile of the FP32 kernels in three bfloat16 parts for a pass (0 forward, 1 backward-data, 2 backward-weight): t[0 .. 3] as
-// conv1d::SplitTile; returns 0 where the pass cannot run on them.
+// Tile of the FP32 kernels in three bfloat16 parts for a pass (0 forward, 1 backward-data, 2 backward-weight): t[0 .. 4] as
+// conv1d::SplitTile (without its roundings); returns 0 where the pass cannot run on them.
 extern "C" int hostmodel_split_tile(int pass, int N, int C, int K, int W, int S, int d, int P, long* t) {
     const int Q = W + 2 * P - (S - 1) * d;
     conv1d::SplitTile r{};
@@ -196,7 +196,7 @@ extern "C" int hostmodel_split_tile(int pass, int N, int C, int K, int W, int S,
         p.P = pass == 0 ? P : (S - 1) * d - P;
         ok = conv1d::split_f32_corr_tile(p, &r);
     }
-    t[0] = r.filter_blocks; t[1] = r.columns_or_taps; t[2] = r.planes_or_units; t[3] = r.grid;
+    t[0] = r.filter_blocks; t[1] = r.columns_or_taps; t[2] = r.planes_or_units; t[3] = r.grid; t[4] = r.x_slots;
     return ok;
 }
 

@@ -24,7 +24,8 @@ PASSES = ("fwd", "bwd_data", "bwd_weight")
 
 # pass, tile, N  C  K  W  S  d  P.  tile: filter blocks of 16 and column blocks of 64 of a workgroup, planes of 8 channels of
 # a step; for the weight gradient filter blocks, taps of a wave, units of the longest strip (the CPU test of the library's
-# bounds model checks that these are the tiles taken).  Widths of the output are odd and end inside a tile, filters end
+# bounds model checks that these are the tiles taken, and that the kernel of one filter block, whose threads hold one to
+# three slots of x, is there with each number of slots).  Widths of the output are odd and end inside a tile, filters end
 # inside a block, and groups of filter blocks lack one.
 TILES = [
     ("fwd",        (1, 1, 2),  (1, 14, 8, 111, 9, 16, 9)),
@@ -61,6 +62,15 @@ TILES = [
     ("bwd_weight", (1, 3, 4),  (39, 4, 66, 821, 9, 3, 27)),
     ("bwd_weight", (1, 7, 2),  (48, 5, 35, 189, 13, 16, 195)),
     ("bwd_weight", (1, 7, 3),  (46, 5, 106, 193, 13, 3, 18)),
+    ("bwd_weight", (1, 3, 2),  (1, 28, 4, 511, 1, 10, 0)),
+    ("bwd_weight", (1, 3, 2),  (46, 4, 5, 1503, 41, 17, 0)),
+    ("bwd_weight", (1, 5, 2),  (59, 27, 34, 300, 28, 11, 0)),
+    ("bwd_weight", (1, 5, 2),  (28, 33, 34, 787, 50, 16, 0)),
+    ("bwd_weight", (1, 7, 2),  (29, 39, 34, 403, 41, 10, 0)),
+    ("bwd_weight", (1, 9, 2),  (49, 5, 40, 465, 43, 9, 0)),
+    ("bwd_weight", (1, 9, 2),  (24, 4, 6, 4699, 16, 16, 205)),
+    ("bwd_weight", (1, 13, 2), (45, 6, 4, 2291, 25, 11, 130)),
+    ("bwd_weight", (1, 13, 2), (55, 36, 23, 63, 49, 14, 306)),
     ("bwd_weight", (2, 2, 3),  (5, 202, 163, 21, 6, 3, 0)),
     ("bwd_weight", (2, 3, 6),  (11, 132, 269, 318, 22, 15, 0)),
     ("bwd_weight", (2, 5, 14), (27, 170, 233, 353, 33, 11, 0)),

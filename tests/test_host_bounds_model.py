@@ -142,9 +142,10 @@ def test_seeded_random_few_tap_small_dilation(model):
 
 
 def _split_tile(lib, ps, geom):
-    """(filter blocks, column blocks or taps per wave, planes or units per strip, workgroups) of the FP32 kernels in
-    three bfloat16 parts; None where they do not take the pass."""
-    t = (ctypes.c_long * 4)()
+    """(filter blocks, column blocks or taps per wave, planes or units per strip, workgroups, slots of x a thread holds)
+    of the FP32 kernels in three bfloat16 parts; None where they do not take the pass.  The slots tell the two
+    weight-gradient kernels apart (none: the one of several filter blocks)."""
+    t = (ctypes.c_long * 5)()
     return tuple(t) if lib.hostmodel_split_tile(ps, *geom, t) else None
 
 
@@ -157,19 +158,26 @@ def test_three_part_tiles_of_the_parity_cases(model):
     seen = set()
     for i, (what, tile, geom) in enumerate(t.TILES):
         ps = t.PASSES.index(what)
-        assert _split_tile(model, ps, geom)[:3] == tile, (what, tile, geom)
-        seen.add((ps == 2,) + tile[:2])
+        taken = _split_tile(model, ps, geom)
+        assert taken[:3] == tile, (what, tile, geom)
+        assert ps < 2 or (tile[0] == 1) == (taken[4] > 0), (tile, geom)
+        seen.add((ps == 2,) + tile[:2] + taken[4:])
         _check(model, geom, 0, passes=(ps,), placements=(i % 3,))
     for geom in t.EDGES + t.QUADS:
         _check(model, geom, 0, passes=(0, 1, 2), placements=(0,))
     rng = np.random.default_rng(3)
-    for _ in range(3000):
+    for _ in range(6000):
         geom = tuple(int(v) for v in (rng.integers(1, 65), np.exp(rng.uniform(0, 5.7)), np.exp(rng.uniform(0, 5.7)),
                                       np.exp(rng.uniform(3, 11)), rng.integers(1, 53), rng.integers(1, 17), 0))
         if geom[3] > (geom[4] - 1) * geom[5]:
             for ps in range(3):
                 tile = _split_tile(model, ps, geom)
-                assert tile is None or (ps == 2,) + tile[:2] in seen, (ps, geom, tile)
+                assert tile is None or (ps == 2,) + tile[:2] + tile[4:] in seen, (ps, geom, tile)
+    # layers whose fastest tile among those of several filter blocks has one block
+    for geom in [(18, 199, 210, 5253, 50, 1, 24), (47, 295, 202, 17163, 35, 20, 340), (34, 209, 239, 740, 41, 20, 400),
+                 (48, 210, 208, 8788, 39, 16, 304), (5, 170, 360, 2597, 6, 24, 60)]:
+        tile = _split_tile(model, 2, geom)
+        assert tile[0] == 1 and tile[4] > 0 and (True,) + tile[:2] + tile[4:] in seen, (geom, tile)
 
 
 def _roundings(lib, geom):
