@@ -166,12 +166,11 @@ bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t);
 // FP32 backward-weight the same way; workspace and second stage of smallc_wgrad_f32_blocks_*
 bool split_f32_wgrad_supported(const WgradProblem& p);
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken);
-// the same with two or four blocks of filters per workgroup, which that launch leaves some layers to
-bool split_f32_wgrad_pair_taken(const WgradProblem& p);
+// the same with two or four blocks of filters per workgroup, which that launch asks first: it takes some layers
 // roundings of a sum in the tile it would take, whether it is left the layer or not, before the second stage; 0: takes none
 double split_f32_wgrad_pair_roundings(const WgradProblem& p);
 bool split_f32_wgrad_pair_tile(const WgradProblem& p, SplitTile* t);
-hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st);
+hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st, bool* taken);
 
 // backward of the fused epilogue: one bit per element of a ReLU's output (element i: bit i & 7 of byte i >> 3), and the masked
 // gradient (in dy unless dy is null) with its sum per filter (in dbias unless that is null)

@@ -47,6 +47,22 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// transposing LDS read: 16 lanes hand in the addresses of 8 bytes each and get these 16 rows of four elements transposed
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+__device__ __forceinline__ u32x2 read_tr(const u32x2* p) {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
+}
+
+// keeps the compiler from knowing how a running index came about (or it keeps one register per address that it could be)
+__device__ __forceinline__ void opaque(int& v) {
+#ifndef HOSTMODEL
+    asm volatile("" : "+v"(v));
+#endif
+}
+
+constexpr size_t kLdsAll = 160 * 1024;
+
 // Shortest sum taken, and the only rule: what has more terms and fits in LDS runs here, for any number of channels,
 // filters, columns and samples.  (A rule that asked how many samples there are would give a sample other bits in another
 // batch.)

@@ -21,7 +21,6 @@ namespace {
 using namespace sp;
 
 constexpr int kThreads = 256;
-constexpr size_t kLdsAll = 160 * 1024;
 
 struct SpArgs {
     const float* in;

@@ -24,7 +24,6 @@ namespace {
 using namespace sp;
 
 constexpr int kRole = 512;  // threads that multiply, and as many that stage
-constexpr size_t kLdsAll = 160 * 1024;
 constexpr int kMaxUnit = kRole / 2;  // positions: a staging thread has one 16-byte slot of dy
 constexpr int kXTasks = 3;           // and at most so many of x
 // Two running sums of a tap, one for every other unit, where the registers allow: half as many roundings of each.
@@ -42,17 +41,6 @@ struct SwfArgs {
 };
 
 typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_at4;  // four floats from any float on
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
-__device__ __forceinline__ u32x2 read_tr(const u32x2* p) {
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
-}
-
-__device__ __forceinline__ void opaque(int& v) {
-#ifndef HOSTMODEL
-    asm volatile("" : "+v"(v));
-#endif
-}
 
 // XT: slots of x of a staging thread
 template <int NTW, int XT>
@@ -459,21 +447,24 @@ hipError_t run(const Plan& pl, hipStream_t st) {
 
 }  // namespace
 
-bool split_f32_wgrad_supported(const WgradProblem& p) { return make_plan(p).ok; }
-
 bool split_f32_wgrad_tile(const WgradProblem& p, SplitTile* t) {
-    if (make_plan(p).ok && split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_tile(p, t);
+    if (split_f32_wgrad_pair_tile(p, t)) return true;
     const Plan pl = make_plan(p);
-    *t = SplitTile{1, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, pl.roundings, cdiv(pl.a.lx, kRole / 2)};
+    if (pl.ok) *t = SplitTile{1, pl.ntw, cdiv(pl.a.nunits, pl.a.strips), pl.grid, pl.roundings, cdiv(pl.a.lx, kRole / 2)};
     return pl.ok;
 }
 
+bool split_f32_wgrad_supported(const WgradProblem& p) {
+    SplitTile t;
+    return split_f32_wgrad_tile(p, &t);
+}
+
 hipError_t split_f32_wgrad_launch(const WgradProblem& p, hipStream_t st, bool* taken) {
+    hipError_t e = split_f32_wgrad_pair_launch(p, st, taken);
+    if (*taken) return e;
     const Plan pl = make_plan(p);
     *taken = pl.ok;
     if (!pl.ok) return hipSuccess;
-    if (split_f32_wgrad_pair_taken(p)) return split_f32_wgrad_pair_launch(p, st);
-    hipError_t e;
     switch (pl.ntw) {
         case 3: e = run<3>(pl, st); break;
         case 5: e = run<5>(pl, st); break;

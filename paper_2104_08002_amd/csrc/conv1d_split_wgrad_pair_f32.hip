@@ -19,7 +19,6 @@ namespace {
 using namespace sp;
 
 constexpr int kThreads = 512;
-constexpr size_t kLdsAll = 160 * 1024;
 // 16-byte slots of dy and x a thread stages per unit, and register sets
 constexpr int kDyTasks = 2, kXTasks = 3;
 constexpr int num_sets(int fbw, int ntw) { return fbw * ntw <= 6 ? 2 : 1; }
@@ -32,18 +31,6 @@ struct SwfArgs {
     long x_sn, dy_sn;
     int qc_sh, upr, nunits, strips, tw_sh, tgroups, kgroups, cblocks, lx, vec;
 };
-
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
-__device__ __forceinline__ u32x2 read_tr(const u32x2* p) {
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
-}
-
-__device__ __forceinline__ void opaque(int& v) {
-#ifndef HOSTMODEL
-    asm volatile("" : "+v"(v));
-#endif
-}
 
 template <int FBW, int NTW>
 __global__ __launch_bounds__(kThreads, 2) void split_wgrad_pair_f32_kernel(SwfArgs a) {
@@ -266,7 +253,7 @@ struct Plan {
 };
 
 // Filter blocks and taps of a wave.  Shapes of one block are priced, not run: where one of them would be the fastest, the
-// kernel that has waves for each is faster still (see split_f32_wgrad_pair_taken).
+// kernel that has waves for each is faster still (see taken_plan).
 constexpr int kShapes[][2] = {{1, 3}, {1, 5}, {1, 7}, {1, 9}, {1, 13}, {2, 2}, {2, 3}, {2, 5}, {2, 7}, {2, 9}, {4, 2}, {4, 3}};
 
 Plan make_plan(const WgradProblem& p) {
@@ -348,39 +335,42 @@ hipError_t run(const Plan& pl, hipStream_t st) {
     return launch_kernel(kern, dim3(pl.grid), dim3(kThreads), pl.lds, st, pl.a);
 }
 
-}  // namespace
-
 // Layers of 129 to 255 pairs of blocks, one workgroup of which would leave up to half of the CUs idle, and of many pairs with
 // a halo of 600 positions and more, over 60 layers drawn from 4 ... 256 channels and 5 ... 51 taps (fewer taps: N = 1, C = K =
 // 200, W = 2000, S = 3 22 us here, 17 in the other kernel).  Not where one block per workgroup is the best that can be done
 // here, one in thirty of them: x is split for that block alone then, and over 19 such layers the other kernel takes 0.47 to
 // 0.97 of the time (N = 5, C = K = 198, W = 6153, S = 49, d = 3 890 and 741 us; N = 1, C = K = 238, W = 232, S = 17, d = 4 29
 // and 14), in one 1.04 (N = 48, C = 210, K = 208, W = 2788, S = 39, d = 16 3170 and 3300), with smaller errors in all.
-bool split_f32_wgrad_pair_taken(const WgradProblem& p) {
+Plan taken_plan(const WgradProblem& p) {
     const long pairs = static_cast<long>(cdiv(p.C, 16)) * cdiv(p.K, 16);
     const bool idle = pairs > 128 && pairs < 256 && p.S >= 5;
     const bool halo = (p.S - 1L) * p.d >= 600 && pairs >= 48;
-    if (!idle && !halo) return false;
-    const Plan pl = make_plan(p);
-    return pl.ok && pl.fbw > 1;
+    if ((!idle && !halo) || static_cast<long>(p.K) * p.Q < 4) return Plan{};
+    Plan pl = make_plan(p);
+    pl.ok = pl.ok && pl.fbw > 1;
+    return pl;
 }
 
-double split_f32_wgrad_pair_roundings(const WgradProblem& p) {
-    const Plan pl = make_plan(p);
+double plan_roundings(const Plan& pl) {
     if (!pl.ok) return 0.0;
     const int WK = 8 >> pl.a.tw_sh;
     return chain_roundings(static_cast<long>((1 << pl.a.qc_sh) / 32 / WK) * cdiv(pl.a.nunits, pl.a.strips)) + chain_roundings(WK);
 }
 
+}  // namespace
+
+double split_f32_wgrad_pair_roundings(const WgradProblem& p) { return plan_roundings(make_plan(p)); }
+
 bool split_f32_wgrad_pair_tile(const WgradProblem& p, SplitTile* t) {
-    const Plan pl = make_plan(p);
-    *t = SplitTile{pl.fbw, pl.ntw, pl.ok ? cdiv(pl.a.nunits, pl.a.strips) : 0, pl.grid, split_f32_wgrad_pair_roundings(p), 0};
+    const Plan pl = taken_plan(p);
+    if (pl.ok) *t = SplitTile{pl.fbw, pl.ntw, cdiv(pl.a.nunits, pl.a.strips), pl.grid, plan_roundings(pl), 0};
     return pl.ok;
 }
 
-hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st) {
-    const Plan pl = make_plan(p);
-    if (!pl.ok) return hipErrorInvalidValue;
+hipError_t split_f32_wgrad_pair_launch(const WgradProblem& p, hipStream_t st, bool* taken) {
+    const Plan pl = taken_plan(p);
+    *taken = pl.ok;
+    if (!pl.ok) return hipSuccess;
     hipError_t e;
     switch (pl.fbw * 16 + pl.ntw) {
         case 32 + 2: e = run<2, 2>(pl, st); break;
