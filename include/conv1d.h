@@ -69,8 +69,7 @@
  *   FP32 product is within 6e-8.
  *   A value is carried to 2^-133, so one below 2^-110 has fewer than 24 bits;
  *   an infinite input makes the outputs it contributes to NaN.  Shorter sums,
- *   weight gradients of samples with K*Q < 4 outputs and layers whose window
- *   does not fit in LDS so, use FP32 products.
+ *   and layers whose window does not fit in LDS so, use FP32 products.
  *   FP32 results of conv1d_fwd and conv1d_bwd_data for a sample have the same
  *   bits whatever other samples the call has.
  *

@@ -256,6 +256,9 @@ struct Plan {
 // kernel that has waves for each is faster still (see taken_plan).
 constexpr int kShapes[][2] = {{1, 3}, {1, 5}, {1, 7}, {1, 9}, {1, 13}, {2, 2}, {2, 3}, {2, 5}, {2, 7}, {2, 9}, {4, 2}, {4, 3}};
 
+// the other kernel loads dy by four elements of a sample
+bool few_outputs(const WgradProblem& p) { return static_cast<long>(p.K) * p.Q < 4; }
+
 Plan make_plan(const WgradProblem& p) {
     Plan best{};
     if (p.bf16 || p.dw_sc != p.S || static_cast<long>(p.N) * p.Q < kMinTerms) return best;
@@ -279,7 +282,7 @@ Plan make_plan(const WgradProblem& p) {
     }
     for (const auto& sh : kShapes) {
         const int fbw = sh[0], ntw = sh[1];
-        if (fbw > 1 && ntw > 2 && fbw / 2 >= kblocks) continue;  // half the filter blocks would do: such a shape loses anyway
+        if (few_outputs(p) ? fbw != 2 : fbw > 1 && ntw > 2 && fbw / 2 >= kblocks) continue;  // half the filter blocks would do: such a shape loses anyway
         const int kgroups = cdiv(kblocks, fbw);
         for (int tw_sh = 0; tw_sh <= 3; ++tw_sh) {
             const int taps = ntw << tw_sh, tgroups = cdiv(p.S, taps), WK = 8 >> tw_sh;
@@ -341,11 +344,13 @@ hipError_t run(const Plan& pl, hipStream_t st) {
 // here, one in thirty of them: x is split for that block alone then, and over 19 such layers the other kernel takes 0.47 to
 // 0.97 of the time (N = 5, C = K = 198, W = 6153, S = 49, d = 3 890 and 741 us; N = 1, C = K = 238, W = 232, S = 17, d = 4 29
 // and 14), in one 1.04 (N = 48, C = 210, K = 208, W = 2788, S = 39, d = 16 3170 and 3300), with smaller errors in all.
+// And samples of one to three outputs, of whose dy the other kernel cannot load four elements (N = 56, C = 256, K = 1,
+// W = 303, S = 51, d = 6 26 us, on FP32 products 93; N = 16, C = 4, K = 1, W = 9, S = 8 9 and 13).
 Plan taken_plan(const WgradProblem& p) {
     const long pairs = static_cast<long>(cdiv(p.C, 16)) * cdiv(p.K, 16);
     const bool idle = pairs > 128 && pairs < 256 && p.S >= 5;
     const bool halo = (p.S - 1L) * p.d >= 600 && pairs >= 48;
-    if ((!idle && !halo) || static_cast<long>(p.K) * p.Q < 4) return Plan{};
+    if (!idle && !halo && !few_outputs(p)) return Plan{};
     Plan pl = make_plan(p);
     pl.ok = pl.ok && pl.fbw > 1;
     return pl;

@@ -188,6 +188,19 @@ def test_weight_gradients_read_by_four(binding, oracle, case):
     assert err <= _bound(2, wl, (0, 0, 8)) and norm <= NORM_BOUND, (err, norm)
 
 
+# weight gradients of samples of one to three outputs
+FEW_OUTPUTS = [(56, 256, 1, 303, 51, 6, 0), (16, 4, 1, 9, 8, 1, 0), (16, 17, 2, 5, 5, 1, 0), (16, 17, 3, 5, 5, 1, 0), (64, 64, 1, 4, 3, 1, 0), (1024, 32, 1, 17, 17, 1, 1)]
+
+
+@pytest.mark.parametrize("case", FEW_OUTPUTS, ids=lambda c: "x".join(map(str, c)))
+def test_weight_gradients_of_few_outputs(binding, oracle, case):
+    wl = _workload(case)
+    assert wl.K * wl.Q < 4 and "split" in binding.conv1d_kernel_name(2, *wl.geometry(), 0)
+    data = inputs.make_inputs(wl)
+    err, norm = _errors(oracle, wl, data, gpu_passes(wl, to_device(wl, data), passes=("bwd_weight",)))["bwd_weight"]
+    assert err <= _bound(2, wl, (0, 0, 8)) and norm <= NORM_BOUND, (err, norm)
+
+
 # layers whose fastest tile has half the running sums, and the roundings of their sums in all strips: 2.3e-7 and 2.3e-7 so
 MANY_ROUNDINGS = [((33, 160, 160, 957, 33, 12, 192), 28.6), ((2, 133, 133, 28080, 33, 10, 160), 34.6)]
 

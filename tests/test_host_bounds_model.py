@@ -163,7 +163,9 @@ def test_three_part_tiles_of_the_parity_cases(model):
         assert ps < 2 or (tile[0] == 1) == (taken[4] > 0), (tile, geom)
         seen.add((ps == 2,) + tile[:2] + taken[4:])
         _check(model, geom, 0, passes=(ps,), placements=(i % 3,))
-    for geom in t.EDGES + t.QUADS:
+    for geom in t.FEW_OUTPUTS:
+        assert _split_tile(model, 2, geom) is not None, geom
+    for geom in t.EDGES + t.QUADS + t.FEW_OUTPUTS[1:]:
         _check(model, geom, 0, passes=(0, 1, 2), placements=(0,))
     rng = np.random.default_rng(3)
     for _ in range(6000):
