@@ -65,7 +65,7 @@ struct GradArgs {
     void* dy;                       // nullptr: not wanted (equal to gy)
     float* partial;                 // [K][N][chunks]; nullptr: no bias
     int N, K, Q, chunks, vec_in, vec_out;
-    long units;                     // N * K * chunks
+    long first, units;              // first of the launch, and all of them: N * K * chunks
 };
 
 // A wave has one chunk of one row (n, k).  Groups of 8 elements are counted over the whole tensor, so that they are aligned
@@ -73,7 +73,7 @@ struct GradArgs {
 template <bool IN16, bool OUT16>
 __global__ __launch_bounds__(kThreads) void epilogue_grad_kernel(GradArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
-    const long unit = static_cast<long>(blockIdx.x) * (kThreads / kWave) + (threadIdx.x >> 6);
+    const long unit = a.first + static_cast<long>(blockIdx.x) * (kThreads / kWave) + (threadIdx.x >> 6);
     if (unit >= a.units) return;
     const long row = unit / a.chunks, chunk = unit - row * a.chunks;
     const long r0 = row * a.Q, r1 = r0 + a.Q, n_all = static_cast<long>(a.N) * a.K * a.Q;
@@ -156,17 +156,25 @@ long row_chunks(int Q) { return ((static_cast<long>(Q) + 14) / 8 + kChunk - 1) /
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// workgroups of a launch: what is more is launched in pieces
+constexpr long kMostBlocks = 0x7fffffffL / kThreads;
+
 }  // namespace
 
 size_t epilogue_grad_workspace(int N, int K, int Q) { return 4 * static_cast<size_t>(N) * K * row_chunks(Q); }
 
 hipError_t relu_mask_launch(const void* y, int bf16, unsigned char* positive, long n, hipStream_t st) {
-    const long blocks = (n + 8L * kThreads * kInFlight - 1) / (8L * kThreads * kInFlight);
-    if (blocks > 0x7fffffffL / kThreads) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
+    constexpr long per_block = 8L * kThreads * kInFlight;
     const int vec = aligned16(y);
-    return bf16 ? launch_kernel(relu_mask_kernel<true>, grid, block, 0, st, y, positive, n, vec)
-                : launch_kernel(relu_mask_kernel<false>, grid, block, 0, st, y, positive, n, vec);
+    for (long at = 0; at < n; at += kMostBlocks * per_block) {
+        const long left = n - at, blocks = (left + per_block - 1) / per_block;
+        const dim3 grid(static_cast<unsigned>(blocks < kMostBlocks ? blocks : kMostBlocks));
+        const void* from = static_cast<const char*>(y) + at * (bf16 ? 2 : 4);
+        const hipError_t e = launch_kernel(bf16 ? relu_mask_kernel<true> : relu_mask_kernel<false>, grid, dim3(kThreads), 0, st, from,
+                                           positive + at / 8, left, vec);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t epilogue_grad_launch(const void* gy, int in16, const unsigned char* positive, void* dy, int out16, float* dbias, float* ws,
@@ -179,18 +187,16 @@ hipError_t epilogue_grad_launch(const void* gy, int in16, const unsigned char* p
     a.vec_in = aligned16(gy);
     a.vec_out = aligned16(dy);
     a.units = static_cast<long>(N) * K * chunks;
-    const long blocks = (a.units + kThreads / kWave - 1) / (kThreads / kWave);
-    if (blocks > 0x7fffffffL / kThreads) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    hipError_t e;
-    if (in16) {
-        if (!out16) return hipErrorInvalidValue;
-        e = launch_kernel(epilogue_grad_kernel<true, true>, grid, block, 0, st, a);
-    } else {
-        e = out16 ? launch_kernel(epilogue_grad_kernel<false, true>, grid, block, 0, st, a)
-                  : launch_kernel(epilogue_grad_kernel<false, false>, grid, block, 0, st, a);
+    if (in16 && !out16) return hipErrorInvalidValue;
+    auto kern = in16 ? epilogue_grad_kernel<true, true> : out16 ? epilogue_grad_kernel<false, true> : epilogue_grad_kernel<false, false>;
+    constexpr long per_block = kThreads / kWave;
+    for (a.first = 0; a.first < a.units; a.first += kMostBlocks * per_block) {
+        const long blocks = (a.units - a.first + per_block - 1) / per_block;
+        const dim3 grid(static_cast<unsigned>(blocks < kMostBlocks ? blocks : kMostBlocks));
+        const hipError_t e = launch_kernel(kern, grid, dim3(kThreads), 0, st, a);
+        if (e != hipSuccess) return e;
     }
-    if (e != hipSuccess || !dbias) return e;
+    if (!dbias) return hipSuccess;
     return launch_kernel(bias_grad_kernel, dim3(static_cast<unsigned>(K)), dim3(kWave), 0, st, ws, dbias, static_cast<long>(N) * chunks);
 }
 

@@ -177,6 +177,7 @@ extern "C" const char* hostmodel_kernel_name(int pass, int N, int C, int K, int 
 }
 
 extern "C" int hostmodel_launches() { return g_launches; }
+extern "C" void hostmodel_reset_launches() { g_launches = 0; }
 
 // Tile of the FP32 kernels in three bfloat16 parts for a pass (0 forward, 1 backward-data, 2 backward-weight): t[0 .. 4] as
 // conv1d::SplitTile (without its roundings); returns 0 where the pass cannot run on them.

@@ -48,6 +48,30 @@ def test_epilogue_backward(binding, N, K, Q, types, relu):
         assert binding.conv1d_epilogue_bwd(gy, pos, tout, False)[1] is None
 
 
+def test_more_rows_than_a_launch_has_waves(binding):
+    """33.6 million rows of a layer with bias and ReLU: one wave each, more than one launch takes."""
+    import torch
+
+    from paper_2104_08002_amd import autograd
+
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    N, K = 2100000, 16
+    x = torch.randn((N, 1, 2), generator=gen, device="cuda").requires_grad_(True)
+    w = torch.randn((K, 1, 1), generator=gen, device="cuda").requires_grad_(True)
+    b = torch.randn(K, generator=gen, device="cuda").requires_grad_(True)
+    y = autograd.conv1d(x, w, b, 1, 0, relu=True)
+    gy = torch.randn(y.shape, generator=gen, device="cuda")
+    dx, dw, db = torch.autograd.grad(y, (x, w, b), gy)
+    g = gy * (y > 0)
+    pos = binding.conv1d_relu_mask(y.detach())
+    assert torch.equal(binding.conv1d_epilogue_bwd(gy, pos, torch.float32, False)[0], g)
+    rx, rw = binding.conv1d_bwd(x.detach(), g, w.detach(), 1, 0)
+    assert torch.equal(dx, rx) and torch.equal(dw, rw)
+    # two elements of a row are added before the sum goes on in 64 bits
+    ref, mag = g.double().sum((0, 2)), g.double().abs().sum((0, 2))
+    assert ((db.double() - ref).abs() <= 2 * 2.0 ** -24 * mag).all()
+
+
 def test_nan_and_infinity_of_a_gradient_stay(binding):
     import torch
 

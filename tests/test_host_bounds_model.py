@@ -274,6 +274,33 @@ def test_the_model_finds_a_planted_off_by_one():
     assert _run(_load(hostmodel_build.build()), 0, geom, 1)[0] == 0
 
 
+def test_backward_of_the_epilogue_in_pieces():
+    """More workgroups than one launch takes are launched in pieces.  In a model that takes three per launch: the mask and
+    the masked gradient (every thread's own elements, so the model has their values) are those of the definition."""
+    import build as hostmodel_build
+
+    lib = _load(hostmodel_build.build(mutate={"conv1d_epilogue_bwd.hip": lambda t: t.replace("0x7fffffffL / kThreads", "3")},
+                                      tag="pieces"))
+    vp, sz = ctypes.c_void_p, ctypes.c_size_t
+    lib.conv1d_relu_mask.argtypes = [vp, vp, sz, ctypes.c_int, vp]
+    lib.conv1d_epilogue_bwd.argtypes = [vp] * 5 + [sz] + [ctypes.c_int] * 5 + [vp]
+    rng = np.random.default_rng(4)
+    for N, K, Q, mask_launches, launches in [(5, 7, 3, 1, 4), (3, 5, 5001, 4, 4), (2, 13, 8192, 9, 8), (1, 12, 17, 1, 2), (1, 13, 17, 1, 3)]:
+        y = np.maximum(rng.standard_normal((N, K, Q)), 0).astype(np.float32)
+        gy = rng.standard_normal((N, K, Q)).astype(np.float32)
+        dy, db = np.full_like(gy, np.nan), np.zeros(K, np.float32)
+        bits, ws = np.full((y.size + 7) // 8, 255, np.uint8), np.empty(1 << 20, np.uint8)
+        lib.hostmodel_reset_launches()
+        assert lib.conv1d_relu_mask(y.ctypes.data, bits.ctypes.data, y.size, 0, None) == 0
+        assert lib.hostmodel_launches() == mask_launches
+        assert (np.unpackbits(bits, bitorder="little")[:y.size].reshape(y.shape) == (y > 0)).all()
+        lib.hostmodel_reset_launches()
+        assert lib.conv1d_epilogue_bwd(gy.ctypes.data, bits.ctypes.data, dy.ctypes.data, db.ctypes.data, ws.ctypes.data, ws.size,
+                                       N, K, Q, 0, 0, None) == 0
+        assert lib.hostmodel_launches() == launches
+        assert (dy == gy * (y > 0)).all(), (N, K, Q)
+
+
 def test_multiply_high_division_is_exact(model):
     """The kernels divide small indices by launch constants with one multiply-high; the host accepts a divisor only with
     the largest dividend it was checked for.  Every accepted (divisor, bound) pair is compared with the plain quotient
