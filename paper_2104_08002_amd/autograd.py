@@ -7,6 +7,7 @@ paper's single-layer measurements use (Section 4.3: ``net.forward(x)`` and ``out
 from __future__ import annotations
 
 import torch
+from torch.autograd import forward_ad
 
 from . import binding
 
@@ -37,7 +38,8 @@ class Conv1dFunction(torch.autograd.Function):
         x, w = ctx.saved_tensors
         d, P = ctx.geometry
         positive = ctx.y_positive if ctx.relu else None
-        if gy.requires_grad and torch.is_grad_enabled():   # create_graph: the bias gradient is differentiable in gy
+        # create_graph or forward mode over this pass: the bias gradient is differentiable in gy
+        if (gy.requires_grad and torch.is_grad_enabled()) or forward_ad.unpack_dual(gy).tangent is not None:
             dy = gy
             if positive is not None:
                 bit = torch.arange(8, dtype=torch.uint8, device=gy.device)

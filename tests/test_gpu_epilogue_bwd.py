@@ -117,7 +117,17 @@ def test_layer_gradients(binding, dtype):
     y = autograd.conv1d(x, w, b, 2, 6, relu=True)
     gy = torch.randn(y.shape, generator=gen, device="cuda").requires_grad_(True)
     db, = torch.autograd.grad(y, b, gy, create_graph=True)
-    back, = torch.autograd.grad(db.sum(), gy)
+    back, = torch.autograd.grad(db.sum(), gy, retain_graph=True)
     assert torch.equal(back, positive.float())
     with torch.no_grad():
         assert torch.equal(autograd.conv1d(x, w, b, 2, 6, relu=True), y)
+    # and forward mode over the backward: the tangent of the bias gradient is that of gy, masked and summed
+    tangent = torch.randn(y.shape, generator=gen, device="cuda")
+    with torch.autograd.forward_ad.dual_level():
+        dual = torch.autograd.forward_ad.make_dual(gy.detach(), tangent)
+        db, = torch.autograd.grad(y, b, dual)
+        db, dt = torch.autograd.forward_ad.unpack_dual(db)
+    assert dt is not None
+    for got, of in ((db, gy.detach()), (dt, tangent)):
+        ref = (of * positive).double()
+        assert ((got.double() - ref.sum((0, 2))).abs() <= 1000 * 2.0 ** -24 * ref.abs().sum((0, 2))).all()  # (torch adds 1000 floats)
