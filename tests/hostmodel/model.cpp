@@ -57,6 +57,13 @@ void free_region(Region& r) {
     r = Region{};
 }
 
+// the same with the last byte right before the guard, whatever alignment beyond `align` that leaves
+Region make_exact(size_t bytes, size_t align, const char* name) {
+    Region r = make_region(bytes, true, name);
+    if (r.map) r.data = r.map + r.map_bytes - kGuard - (bytes + align - 1) / align * align;
+    return r;
+}
+
 void on_fault(int, siginfo_t* info, void*) {
     if (!g_armed) _exit(139);
     g_fault_addr = info->si_addr;
@@ -67,6 +74,47 @@ void on_fault(int, siginfo_t* info, void*) {
 int g_launches = 0;  // kernel launches of the last hostmodel_run
 
 void* dynamic_lds() { return g_lds.data; }
+
+// Runs a call of the library with faults caught: 0, 100 - its status, or 1 with a message about the access that left its
+// tensor.
+template <typename Call>
+int guarded(int pass, char* msg, int msglen, Call call) {
+    struct sigaction sa, old_segv, old_bus;
+    memset(&sa, 0, sizeof(sa));
+    sa.sa_sigaction = on_fault;
+    sa.sa_flags = SA_SIGINFO | SA_NODEFER;
+    sigaction(SIGSEGV, &sa, &old_segv);
+    sigaction(SIGBUS, &sa, &old_bus);
+    g_launches = 0;
+    int rc;
+    if (sigsetjmp(g_jump, 1) == 0) {
+        g_armed = 1;
+        const int st = call();
+        g_armed = 0;
+        rc = st == CONV1D_OK ? 0 : 100 - st;
+    } else {
+        g_armed = 0;
+        const char* fa = static_cast<const char*>(g_fault_addr);
+        const char* where = "no tensor of this call";
+        long off = 0;
+        for (const auto& r : g_regions)
+            if (fa >= r.map && fa < r.map + r.map_bytes) {
+                where = r.name;
+                off = fa - r.data;
+            }
+        if (g_lds.map && fa >= g_lds.map && fa < g_lds.map + g_lds.map_bytes) {
+            where = g_lds.name;
+            off = fa - g_lds.data;
+        }
+        if (msg && msglen > 0)
+            snprintf(msg, msglen, "access outside %s (address %p, byte offset %ld from its start) by workgroup (%u,%u) thread %u of a kernel of pass %d",
+                     where, static_cast<const void*>(fa), off, g_block.x, g_block.y, g_thread.x, pass);
+        rc = 1;
+    }
+    sigaction(SIGSEGV, &old_segv, nullptr);
+    sigaction(SIGBUS, &old_bus, nullptr);
+    return rc;
+}
 
 void run_grid(dim3 grid, dim3 block, size_t lds_bytes, const std::function<void()>& fn) {
     ++g_launches;
@@ -89,7 +137,7 @@ void run_grid(dim3 grid, dim3 block, size_t lds_bytes, const std::function<void(
 using namespace hostmodel;
 
 // pass: 0 conv1d_fwd, 1 conv1d_bwd_data, 2 conv1d_bwd_weight, 3 conv1d_bwd, 4 conv1d_fwd_ex (bias, ReLU, bfloat16 output
-// when dtype is bfloat16), 5 conv1d_bwd_data_ex (bfloat16 output).  placement: 0 tensors end at a guard page, 1 tensors
+// when dtype is bfloat16), 5 conv1d_bwd_data_ex (bfloat16 output), 6 conv1d_bwd_ex (bfloat16 dx).  placement: 0 tensors end at a guard page, 1 tensors
 // start behind one, 2 as 0 with every tensor shifted by one element (the element-aligned paths).
 // Returns 0 (every access inside its tensor), 1 (an access left its tensor; msg says where), or 100 - status when the
 // library refused the call.
@@ -98,7 +146,7 @@ extern "C" int hostmodel_run(int pass, int N, int C, int K, int W, int S, int d,
     const long Q = static_cast<long>(W) + 2L * P - static_cast<long>(S - 1) * d;
     if (Q < 1) return 100 - CONV1D_EINVAL;
     const size_t e = dtype == CONV1D_BF16 ? 2 : 4;
-    const bool out16 = dtype == CONV1D_BF16 && (pass == 4 || pass == 5);
+    const bool out16 = dtype == CONV1D_BF16 && pass >= 4;
     const size_t shift = placement == 2 ? 1 : 0;
     const bool end_aligned = placement != 1;
     const size_t nx = static_cast<size_t>(N) * C * W, ny = static_cast<size_t>(N) * K * Q, nw = static_cast<size_t>(K) * C * S;
@@ -123,53 +171,53 @@ extern "C" int hostmodel_run(int pass, int N, int C, int K, int W, int S, int d,
     if (shift) {  // one element into each allocation: only element alignment is left
         x += e; w += e; dy += e; y += out16 ? 2 : 4; dx += out16 ? 2 : 4; dw += 4;
     }
-    struct sigaction sa, old_segv, old_bus;
-    memset(&sa, 0, sizeof(sa));
-    sa.sa_sigaction = on_fault;
-    sa.sa_flags = SA_SIGINFO | SA_NODEFER;
-    sigaction(SIGSEGV, &sa, &old_segv);
-    sigaction(SIGBUS, &sa, &old_bus);
     conv1d_set_variant(variant);
-    g_launches = 0;
-    int rc;
-    if (sigsetjmp(g_jump, 1) == 0) {
-        g_armed = 1;
-        int st = CONV1D_OK;
+    const int rc = guarded(pass, msg, msglen, [&] {
         switch (pass) {
-            case 0: st = conv1d_fwd(x, w, reinterpret_cast<float*>(y), N, C, K, W, S, d, P, dtype, nullptr); break;
-            case 1: st = conv1d_bwd_data(dy, w, reinterpret_cast<float*>(dx), N, C, K, W, S, d, P, dtype, nullptr); break;
-            case 2: st = conv1d_bwd_weight(x, dy, reinterpret_cast<float*>(dw), ws, wsb, N, C, K, W, S, d, P, dtype, nullptr); break;
-            case 3: st = conv1d_bwd(x, dy, w, reinterpret_cast<float*>(dx), reinterpret_cast<float*>(dw), ws, wsb, N, C, K, W, S, d, P, dtype, nullptr); break;
-            case 4: st = conv1d_fwd_ex(x, w, reinterpret_cast<float*>(bias), y, N, C, K, W, S, d, P, dtype,
-                                       CONV1D_EPI_RELU | (out16 ? CONV1D_EPI_OUT_BF16 : 0), nullptr); break;
-            case 5: st = conv1d_bwd_data_ex(dy, w, dx, N, C, K, W, S, d, P, dtype, out16 ? CONV1D_EPI_OUT_BF16 : 0, nullptr); break;
-            default: st = CONV1D_EINVAL;
+            case 0: return conv1d_fwd(x, w, reinterpret_cast<float*>(y), N, C, K, W, S, d, P, dtype, nullptr);
+            case 1: return conv1d_bwd_data(dy, w, reinterpret_cast<float*>(dx), N, C, K, W, S, d, P, dtype, nullptr);
+            case 2: return conv1d_bwd_weight(x, dy, reinterpret_cast<float*>(dw), ws, wsb, N, C, K, W, S, d, P, dtype, nullptr);
+            case 3: return conv1d_bwd(x, dy, w, reinterpret_cast<float*>(dx), reinterpret_cast<float*>(dw), ws, wsb, N, C, K, W, S, d, P, dtype, nullptr);
+            case 4: return conv1d_fwd_ex(x, w, reinterpret_cast<float*>(bias), y, N, C, K, W, S, d, P, dtype,
+                                         CONV1D_EPI_RELU | (out16 ? CONV1D_EPI_OUT_BF16 : 0), nullptr);
+            case 5: return conv1d_bwd_data_ex(dy, w, dx, N, C, K, W, S, d, P, dtype, out16 ? CONV1D_EPI_OUT_BF16 : 0, nullptr);
+            case 6: return conv1d_bwd_ex(x, dy, w, dx, reinterpret_cast<float*>(dw), ws, wsb, N, C, K, W, S, d, P, dtype,
+                                         out16 ? CONV1D_EPI_OUT_BF16 : 0, nullptr);
+            default: return static_cast<int>(CONV1D_EINVAL);
         }
-        g_armed = 0;
-        rc = st == CONV1D_OK ? 0 : 100 - st;
-    } else {
-        g_armed = 0;
-        const char* fa = static_cast<const char*>(g_fault_addr);
-        const char* where = "no tensor of this call";
-        long off = 0;
-        for (const auto& r : g_regions)
-            if (fa >= r.map && fa < r.map + r.map_bytes) {
-                where = r.name;
-                off = fa - r.data;
-            }
-        if (g_lds.map && fa >= g_lds.map && fa < g_lds.map + g_lds.map_bytes) {
-            where = g_lds.name;
-            off = fa - g_lds.data;
-        }
-        if (msg && msglen > 0)
-            snprintf(msg, msglen, "access outside %s (address %p, byte offset %ld from its start) by workgroup (%u,%u) thread %u of a kernel of pass %d",
-                     where, static_cast<const void*>(fa), off, g_block.x, g_block.y, g_thread.x, pass);
-        rc = 1;
-    }
+    });
     conv1d_set_variant(0);
-    sigaction(SIGSEGV, &old_segv, nullptr);
-    sigaction(SIGBUS, &old_bus, nullptr);
     return rc;
+}
+
+// The backward of the epilogue on N K Q elements: conv1d_relu_mask of an output and conv1d_epilogue_bwd with that mask (when
+// relu), into dy (when want_dy) and dbias (when bias).  placement 0: every
+// tensor ends at a guard page exactly, on the alignment of its elements alone; 1: it starts behind one, 16-byte aligned; 2:
+// it ends at one, 16-byte aligned, up to 15 bytes before it.
+extern "C" int hostmodel_run_epilogue(int N, int K, int Q, int in16, int out16, int relu, int want_dy, int bias, int placement,
+                                      char* msg, int msglen) {
+    const size_t n = static_cast<size_t>(N) * K * Q;
+    for (auto& r : g_regions) free_region(r);
+    g_regions.clear();
+    auto tensor = [&](size_t bytes, size_t align, const char* name) -> char* {
+        g_regions.push_back(placement == 0 ? make_exact(bytes, align, name) : make_region(bytes, placement == 2, name));
+        return g_regions.back().data;
+    };
+    const size_t ei = in16 ? 2 : 4, eo = out16 ? 2 : 4, wsb = conv1d_epilogue_bwd_workspace_bytes(N, K, Q);
+    char* y = tensor(n * ei, ei, "y");
+    char* gy = tensor(n * ei, ei, "gy");
+    char* mask = tensor((n + 7) / 8, 1, "mask");
+    char* dy = tensor(n * eo, eo, "dy");
+    float* db = reinterpret_cast<float*>(tensor(4 * static_cast<size_t>(K), 4, "dbias"));
+    char* ws = tensor(wsb, 4, "workspace");
+    return guarded(7, msg, msglen, [&] {
+        if (relu) {
+            const int st = conv1d_relu_mask(y, mask, n, in16 ? CONV1D_BF16 : CONV1D_FP32, nullptr);
+            if (st != CONV1D_OK) return st;
+        }
+        return conv1d_epilogue_bwd(gy, relu ? mask : nullptr, want_dy ? dy : nullptr, bias ? db : nullptr, bias ? ws : nullptr,
+                                   bias ? wsb : 0, N, K, Q, in16 ? CONV1D_BF16 : CONV1D_FP32, out16 ? CONV1D_BF16 : CONV1D_FP32, nullptr);
+    });
 }
 
 extern "C" const char* hostmodel_kernel_name(int pass, int N, int C, int K, int W, int S, int d, int P, int dtype) {

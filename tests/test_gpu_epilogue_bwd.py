@@ -82,7 +82,13 @@ def test_nan_and_infinity_of_a_gradient_stay(binding):
     assert _same(dy, gy * (y > 0)) and db.isnan().all()
 
 
-@pytest.mark.parametrize("C,K,W,S,d", [(15, 15, 3000, 51, 8), (16, 16, 1000, 51, 4), (40, 24, 901, 7, 3), (64, 64, 2000, 5, 1), (12, 9, 777, 25, 3)])
+# layers whose passes over channel blocks meet in a float dx (the CPU test of the library's bounds model checks that they do,
+# and that the first two below add up the weight gradient within the backward-data launch)
+MEETING = [(40, 24, 901, 7, 3), (100, 100, 301, 3, 3)]
+
+
+@pytest.mark.parametrize("C,K,W,S,d", [(15, 15, 6000, 5, 8), (15, 15, 60000, 51, 8), (15, 15, 3000, 51, 8), (16, 16, 1000, 51, 4), (64, 64, 2000, 5, 1),
+                                       (12, 9, 777, 25, 3)] + MEETING)
 def test_bf16_gradient_of_the_input_is_the_rounded_one(binding, C, K, W, S, d):
     import torch
 
@@ -93,6 +99,10 @@ def test_bf16_gradient_of_the_input_is_the_rounded_one(binding, C, K, W, S, d):
     dx, dw = binding.conv1d_bwd(x, dy, w, d, P)
     dx16, dw16 = binding.conv1d_bwd_ex(x, dy, w, d, P, out_bf16=True)
     assert torch.equal(dx16, dx.bfloat16()) and torch.equal(dw16, dw)
+    if (C, K, W, S, d) in MEETING:
+        with pytest.raises(binding.Conv1dError) as e:
+            binding._bwd(x, dy, w, d, P, None, None, None, None, True)
+        assert e.value.status == binding.STATUS_EUNSUPPORTED
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -14,7 +14,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, os.path.join(HERE, "hostmodel"))
 
-PASS_NAMES = ("fwd", "bwd_data", "bwd_weight", "bwd", "fwd_ex", "bwd_data_ex")
+PASS_NAMES = ("fwd", "bwd_data", "bwd_weight", "bwd", "fwd_ex", "bwd_data_ex", "bwd_ex")
 
 
 def _load(path):
@@ -37,7 +37,7 @@ def _run(lib, ps, geom, dtype, variant=0, placement=0):
     return rc, msg.value.decode()
 
 
-def _check(lib, geom, dtype, passes=range(6), placements=(0, 1), variant=0):
+def _check(lib, geom, dtype, passes=range(7), placements=(0, 1), variant=0):
     ran = 0
     for ps in passes:
         for pl in placements:
@@ -118,7 +118,7 @@ def test_seeded_random_geometries(model):
         geom = _random_geometry(rng)
         dtype = i & 1
         # forward, backward-data and backward-weight always; the combined and fused entry points on every fourth one
-        passes = range(6) if i % 4 == 0 else (0, 1, 2)
+        passes = range(7) if i % 4 == 0 else (0, 1, 2)
         ran += _check(model, geom, dtype, passes=passes, placements=(i // 2 % 2,))
     assert ran >= 2400
 
@@ -272,6 +272,35 @@ def test_the_model_finds_a_planted_off_by_one():
     rc, msg = _run(lib, 0, geom, 1)
     assert rc == 1 and "outside x" in msg, (rc, msg)
     assert _run(_load(hostmodel_build.build()), 0, geom, 1)[0] == 0
+
+
+def test_backward_of_the_epilogue_stays_inside_its_tensors(model):
+    """conv1d_relu_mask and conv1d_epilogue_bwd: rows of every remainder of 8 and around a wave's 512 groups, every remainder
+    of the whole, both types, each output with and without the others, a workspace of the bytes the query names."""
+    msg = ctypes.create_string_buffer(512)
+    model.hostmodel_run_epilogue.argtypes = [ctypes.c_int] * 9 + [ctypes.c_char_p, ctypes.c_int]
+    sizes = [(n, k, q) for q in range(1, 18) for n, k in ((1, 1), (1, 3), (2, 5), (3, 8))]
+    sizes += [(2, 3, q) for q in list(range(4079, 4106)) + [8185, 8191, 8192, 9001]]
+    for i, (N, K, Q) in enumerate(sizes):
+        for in16, out16 in ((0, 0), (1, 1), (0, 1)):
+            for placement in (0, 1, 2):
+                for relu, dy, bias in ((1, 1, 1),) if (i + placement) % 4 else ((1, 1, 1), (0, 1, 1), (1, 1, 0), (0, 0, 1), (1, 0, 1)):
+                    rc = model.hostmodel_run_epilogue(N, K, Q, in16, out16, relu, dy, bias, placement, msg, 512)
+                    assert rc == 0, (N, K, Q, in16, out16, relu, dy, bias, placement, rc, msg.value.decode())
+
+
+def test_launches_of_a_backward_with_bfloat16_dx(model):
+    """Small-channel layers whose backward-data launch is wide enough add up the weight gradient's partial tiles in it, with
+    a bfloat16 dx as with floats: two launches, three with a second stage of its own.  Where passes over channel blocks meet
+    in the output, a bfloat16 one is refused before anything is launched."""
+    for geom, launches in [((2, 15, 15, 6000, 5, 8, 16), 2), ((2, 15, 15, 60000, 51, 8, 200), 2), ((3, 15, 15, 3000, 51, 8, 200), 3)]:
+        for ps in (3, 6):
+            assert _run(model, ps, geom, 1) == (0, "") and model.hostmodel_launches() == launches, (geom, ps, model.hostmodel_launches())
+    import test_gpu_epilogue_bwd as t
+
+    for C, K, W, S, d in t.MEETING:
+        geom = (3, C, K, W, S, d, (S - 1) * d // 2)
+        assert _run(model, 6, geom, 1)[0] == 102 and model.hostmodel_launches() == 0, geom
 
 
 def test_backward_of_the_epilogue_in_pieces():
