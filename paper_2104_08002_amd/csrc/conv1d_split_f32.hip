@@ -273,14 +273,18 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
 // are, so that a sample's result does not depend on its batch.  The least of matrix time plus what steps and windows cost
 // beside it over the tiles of 256 columns and more; workgroups that share a CU hide half of the latter.  -1: none fits.
 // Long rows of many filters and taps take one plane, four taps a step: the windows are short beside the steps then, and their
-// workgroups share CUs three at a time.  S = 51, d = 1, W = 60000, one plane and two: N = 1, C = K = 64 136 and 139 us, 128 473
-// and 499, 256 1772 and 1948; shorter rows lose with one where the batch is small (N = 1, W = 20000, C = K = 64: 83.7 and 81.5)
-// and gain where it is not (N = 4: 172 and 178).
+// workgroups share CUs three at a time.  W = 60000, one plane and two: C = K = 64, d = 1, S = 40 N = 1 115 and 115 us, N = 4 372
+// and 385, S = 47 128 and 130, 424 and 441, S = 51 137 and 139, 456 and 499; C = K = 128, N = 4 S = 43 1520 and 1640, S = 51
+// 1770 and 1910; d = 8 and 16 the same tiles either way, within 0.5 %; N = 2, C = K = 45, W = 55001, S = 43, d = 5 128 and 144.
+// Shorter rows lose with one where the batch is small (N = 1, W = 20000, C = K = 64, S = 51: 83.7 and 81.5) and gain where it is
+// not (N = 4: 172 and 178).  Not where four taps a step pad the taps by more than two do (S = 41, 42, 45, 46, 49, 50): the
+// sums are longer by these zeros, 2 % more error (C = K = 64, S = 41 1.77e-7 and 1.73e-7), for between 2 % more and 8 % less
+// time.
 constexpr int kLongTaps = 40;
 constexpr long kLongRows = 2400000;  // filters x columns of a sample
 
 int planes_shift(const CorrProblem& p) {
-    if (p.S >= kLongTaps && static_cast<long>(p.M) * p.Wout >= kLongRows)
+    if (p.S >= kLongTaps && cdiv(p.S, 4) * 4 <= cdiv(p.S, 2) * 2 && static_cast<long>(p.M) * p.Wout >= kLongRows)
         for (const Tile t : kTiles)
             if (t.pb >= 4 && 16 * (t.fbw - 1) < p.M && fit(p, t, 0).ok) return 0;
     int best = -1;

@@ -45,6 +45,7 @@ TILES = [
     ("bwd_data",   (3, 6, 1),  (34, 72, 8, 2343, 4, 3, 4)),
     ("fwd",        (4, 4, 2),  (47, 21, 101, 771, 2, 2, 5)),
     ("fwd",        (4, 5, 1),  (48, 8, 108, 1292, 4, 1, 6)),
+    ("fwd",        (1, 6, 1),  (1, 16, 161, 15003, 43, 1, 21)),  # rows so long that one plane is taken for that
     ("bwd_weight", (1, 3, 1),  (1, 4, 5, 109, 1, 3, 0)),
     ("bwd_weight", (1, 3, 3),  (43, 4, 4, 3497, 1, 3, 1)),
     ("bwd_weight", (1, 5, 4),  (51, 5, 6, 3856, 4, 3, 0)),
@@ -369,7 +370,7 @@ def test_largest_and_smallest_floats(binding):
 
 # layers of more than 16 channels or filters, of up to 16, of one kind on either side, on the FP32 instruction
 BATCH = [(64, 64, 4000, 5, 2), (100, 100, 1000, 9, 1), (40, 24, 1300, 7, 3), (17, 33, 2000, 15, 4), (15, 15, 5000, 51, 8), (8, 8, 3001, 9, 2),
-         (4, 12, 2500, 25, 1), (64, 16, 4000, 5, 1), (8, 40, 3000, 15, 2), (3, 40, 3000, 5, 3), (3, 2, 5000, 5, 8)]
+         (4, 12, 2500, 25, 1), (64, 16, 4000, 5, 1), (8, 40, 3000, 15, 2), (16, 161, 15001, 43, 2), (3, 40, 3000, 5, 3), (3, 2, 5000, 5, 8)]
 
 
 @pytest.mark.parametrize("case", BATCH, ids=lambda c: "x".join(map(str, c)))

@@ -227,6 +227,14 @@ def test_small_launches_of_the_three_part_kernels_take_small_tiles(model):
         assert small[:2] == (1, 1) and large[0] * large[1] >= 8, (C, K, S, d, small, large)
 
 
+def test_long_rows_of_many_taps_are_not_padded_for_one_plane(model):
+    """Long rows take steps of one plane and four taps, but where that would multiply more taps than two planes do."""
+    for S in range(40, 53):
+        for C, K, W in [(64, 64, 60000), (128, 128, 60000), (16, 161, 15001)]:
+            planes = _split_tile(model, 0, (1, C, K, W, S, 1, S // 2))[2]
+            assert planes == (2 if S % 4 in (1, 2) else 1), (S, C, K, W, planes)
+
+
 def test_weights_of_the_three_part_kernels_stay_within_32_bits(model):
     """Weights are read at 32-bit byte offsets: a layer of 2^30 weights and more is left to the other kernels."""
     for C, K, S, taken in [(8192, 8192, 15, True), (8192, 8192, 16, False), (4096, 8191, 32, True), (4096, 8192, 32, False)]:
