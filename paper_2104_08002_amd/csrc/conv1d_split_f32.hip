@@ -252,8 +252,10 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
     f.nstages = cdiv(p.R, 8 << sh);
     f.wlen = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
     f.columns = f.wlen;
+    auto lds = [&] { return (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16; };
     if (sh > 0) f.wlen = (f.wlen + 15) & ~15L;  // the planes of a read begin in the same bank (C = K = 48, S = 17, d = 3: 40.0 -> 38.8 us)
-    f.lds = (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16;
+    if (lds() > kLdsAll) f.wlen = f.columns;    // (nothing to give away)
+    f.lds = lds();
     if (f.wlen > 16384 || f.lds > kLdsAll) return f;
     const long columns = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * 64 * t.pb;  // the last tile may end behind the row
     if (columns > 1L << 31 || columns - 64 * t.pb - p.P + f.wlen > 1L << 31) return f;  // 32-bit columns in the kernel

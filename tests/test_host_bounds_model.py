@@ -235,6 +235,14 @@ def test_long_rows_of_many_taps_are_not_padded_for_one_plane(model):
             assert planes == (2 if S % 4 in (1, 2) else 1), (S, C, K, W, planes)
 
 
+def test_windows_that_just_fit_are_taken(model):
+    """Planes are rounded up to start in the same bank where LDS has the room, no layer is refused for it."""
+    for ps, geom in [(0, (2, 11, 39, 1392, 2, 1385, 0)), (1, (2, 11, 39, 1392, 2, 1385, 0)), (1, (2, 1, 115, 1380, 2, 1379, 0)), (1, (2, 4, 11, 1383, 2, 1381, 0))]:
+        assert _split_tile(model, ps, geom) is not None, geom
+        for placement in (0, 1, 2):
+            assert _run(model, ps, geom, 0, 0, placement) == (0, "")
+
+
 def test_weights_of_the_three_part_kernels_stay_within_32_bits(model):
     """Weights are read at 32-bit byte offsets: a layer of 2^30 weights and more is left to the other kernels."""
     for C, K, S, taken in [(8192, 8192, 15, True), (8192, 8192, 16, False), (4096, 8191, 32, True), (4096, 8192, 32, False)]:
