@@ -12,6 +12,11 @@ from torch.autograd import forward_ad
 from . import binding
 
 
+def _has_tangent(t) -> bool:
+    # (unpack_dual asks for the level first too, but takes 2 us of a backward to say that there is none)
+    return getattr(forward_ad, "_current_level", 0) >= 0 and forward_ad.unpack_dual(t).tangent is not None
+
+
 class Conv1dFunction(torch.autograd.Function):
     """y = conv1d(x, w[, bias]) with dilation and zero padding; backward = one conv1d_bwd call."""
 
@@ -39,7 +44,7 @@ class Conv1dFunction(torch.autograd.Function):
         d, P = ctx.geometry
         positive = ctx.y_positive if ctx.relu else None
         # create_graph or forward mode over this pass: the bias gradient is differentiable in gy
-        if (gy.requires_grad and torch.is_grad_enabled()) or forward_ad.unpack_dual(gy).tangent is not None:
+        if (gy.requires_grad and torch.is_grad_enabled()) or _has_tangent(gy):
             dy = gy
             if positive is not None:
                 bit = torch.arange(8, dtype=torch.uint8, device=gy.device)
