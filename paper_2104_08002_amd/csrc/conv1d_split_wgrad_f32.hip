@@ -312,6 +312,7 @@ struct Plan {
     int ntw, grid;
     SwfArgs a;
     size_t lds;
+    long most;  // strips that the workspace holds
     double roundings;
 };
 
@@ -334,8 +335,19 @@ double roundings(int ntw, int WK, int steps, long longest) {
     return r;
 }
 
-// the fastest tile of at most so many roundings
-Plan search(const WgradProblem& p, double most_roundings) {
+// The least that any tile of either kernel rounds off: one k-step an addition, in the best number of shares.
+double least_roundings(const WgradProblem& p, long most) {
+    const long steps = static_cast<long>(p.N) * cdiv(p.Q, 32), strips = most < steps ? most : steps, per_strip = (steps + strips - 1) / strips;
+    double least = chain_roundings(per_strip);
+    for (int WK = 2; WK <= 8; WK *= 2) {
+        const double r = chain_roundings((per_strip + WK - 1) / WK) + chain_roundings(WK);
+        if (r < least) least = r;
+    }
+    return least;
+}
+
+// the fastest tile, or the fastest of at most so many roundings
+Plan search(const WgradProblem& p, const double* most_roundings) {
     Plan best{};
     if (p.bf16 || p.dw_sc != p.S || static_cast<long>(p.N) * p.Q < kMinTerms) return best;
     if (static_cast<long>(p.K) * p.Q < 4) return best;  // dy is loaded by four elements of a sample
@@ -379,12 +391,11 @@ Plan search(const WgradProblem& p, double most_roundings) {
                 if (strips > nunits) strips = nunits;
                 // one strip while a few units cost less than the second stage, which it does without
                 if (nunits <= kOneStrip) strips = 1;
-                const long all = most < nunits ? most : nunits;
-                if (strips > 0 && roundings(ntw, WK, steps, (nunits + strips - 1) / strips) > most_roundings) strips = all;
+                if (most_roundings && strips > 0 && roundings(ntw, WK, steps, (nunits + strips - 1) / strips) > *most_roundings)
+                    strips = most < nunits ? most : nunits;
                 if (nunits > 0x3fffffffL || strips < 1 || strips * per_strip > (1 << 20)) continue;
                 const long longest = (nunits + strips - 1) / strips;  // units of the longest strip
-                const double rounded = roundings(ntw, WK, steps, longest);
-                if (rounded > most_roundings) continue;
+                if (most_roundings && roundings(ntw, WK, steps, longest) > *most_roundings) continue;
                 // Cycles of a unit on one SIMD, the products of its two multiplying waves beside what its two staging waves
                 // do; a fit to all tiles on 17 layers (C, K 4 ... 256, 1 ... 51 taps): what is taken is within 9 % of the
                 // fastest, 2 % on average.
@@ -397,7 +408,6 @@ Plan search(const WgradProblem& p, double most_roundings) {
                 best.ok = true;
                 best.ntw = ntw;
                 best.lds = lds;
-                best.roundings = rounded;
                 best.grid = static_cast<int>(strips * per_strip);
                 SwfArgs& a = best.a;
                 a.qc = static_cast<int>(QC); a.upr = upr; a.nunits = static_cast<int>(nunits); a.strips = static_cast<int>(strips);
@@ -407,6 +417,9 @@ Plan search(const WgradProblem& p, double most_roundings) {
     }
     if (!best.ok) return best;
     SwfArgs& a = best.a;
+    best.most = most;
+    const int WK = 8 >> a.tw_sh;
+    best.roundings = roundings(best.ntw, WK, cdiv(a.qc / 32, WK), cdiv(a.nunits, a.strips));
     a.x = static_cast<const float*>(p.x);
     a.dy = static_cast<const float*>(p.dy);
     a.ws = a.strips > 1 ? static_cast<float*>(p.ws) : nullptr;
@@ -422,17 +435,17 @@ Plan search(const WgradProblem& p, double most_roundings) {
 // of this rule and of that kernel: N = 33, C = K = 160, W = 957, S = 33, d = 12 2.3, 1.4 and 1.4, 326, 388 and 727; N = 8,
 // C = 144, K = 160, W = 11290, S = 25, d = 4 2.5, 2.0 and 2.1, 635, 842 and 1319; N = 41, C = 42, K = 40, W = 55280, S = 46,
 // d = 16 3.4, 2.6 and 3.4, 3120, 3060 and 4280.  One layer in 25 takes another tile for it.  A few roundings are less than
-// those of the steps and of the second stage, and are not compared (a second search, 2 us of host time, would show in the
-// short launches that have so few).
+// those of the steps and of the second stage, and are not compared; nor is what no tile can round less often (another search
+// is 1 us of host time, which would show in the short launches that have so few).
 constexpr double kFewRoundings = 8;
 
 Plan make_plan(const WgradProblem& p) {
-    const Plan fastest = search(p, 1e300);
-    if (!fastest.ok || fastest.roundings <= kFewRoundings) return fastest;
+    const Plan fastest = search(p, nullptr);
+    if (!fastest.ok || fastest.roundings <= kFewRoundings || fastest.roundings <= least_roundings(p, fastest.most)) return fastest;
     double most = split_f32_wgrad_pair_roundings(p);
     if (most < kFewRoundings) most = kFewRoundings;
     if (fastest.roundings <= most) return fastest;
-    const Plan fewer = search(p, most);
+    const Plan fewer = search(p, &most);
     return fewer.ok ? fewer : fastest;  // (no layer of 50000 of all kinds was without one)
 }
 
