@@ -362,13 +362,16 @@ Plan search(const WgradProblem& p, const double* most_roundings) {
             if (tw_sh > 0 && tgroups == cdiv(p.S, taps / 2)) continue;  // half the waves would do
             const long per_strip = static_cast<long>(cblocks) * kblocks * tgroups;
             const long halo = static_cast<long>(taps - 1) * p.d;
+            const long turns = (most * per_strip + 255) / 256, one = per_strip < 256 ? 256 / per_strip : 1;
+            long before = 0;
             // units whose x is one, two or three positions per staging thread, and small ones for short rows
             for (int i = 0; i < 6; ++i) {
                 long QC = i < 3 ? ((i + 1) * (kRole / 2) - halo) & ~31L : 32L << (i - 3);
                 const long fits = (static_cast<long>(kLdsAll / 96) - 2 * (halo + 23)) / 4;  // 2 stages of 3 parts
                 if (QC > fits) QC = fits & ~31L;
                 if (QC > kMaxUnit) QC = kMaxUnit;
-                if (QC < 32) continue;
+                if (QC < 32 || QC == before) continue;
+                before = QC;
                 const long lx = QC + halo, lxp = padded(lx);
                 const size_t stage = static_cast<size_t>(3 * (2 * QC + 2 * lxp)) * 16;
                 const size_t red = WK > 1 ? static_cast<size_t>(taps) * (WK / 2) * 1024 : 0;
@@ -377,13 +380,13 @@ Plan search(const WgradProblem& p, const double* most_roundings) {
                 const int steps = cdiv(QC / 32, WK);
                 // one k-step per addition and one running sum: not over more, shorter units than this
                 if (steps == 1 && !two_sums(ntw) && QC < kMaxUnit && QC < p.Q) continue;
-                const int upr = cdiv(p.Q, QC);
+                const int upr = static_cast<int>((static_cast<unsigned>(p.Q) + static_cast<unsigned>(QC) - 1) / static_cast<unsigned>(QC));
                 const long nunits = static_cast<long>(p.N) * upr;
+                if (nunits > 0x3fffffffL) continue;
                 // As many strips as the workspace holds, but no few workgroups over a whole number per CU: six pairs of
                 // blocks in 43 strips took two turns, 34 us, where 42 strips take 26.  One turn at most where the k-steps
                 // that are summed by themselves more than make up for the longer sums of fewer strips (with as many: N = 53,
                 // C = 40, K = 7, W = 9177, S = 51, d = 16 1.8e-7 off where 1.6e-7 in all strips).
-                const long turns = (most * per_strip + 255) / 256, one = per_strip < 256 ? 256 / per_strip : 1;
                 const long by_itself = (steps < 2 ? 1 : steps >= 4 && four_steps(ntw) ? 4 : 2) * (two_sums(ntw) ? 2 : 1);
                 long strips = most;
                 if (turns > 1 && one * by_itself >= 2 * most) strips = one;
@@ -393,8 +396,8 @@ Plan search(const WgradProblem& p, const double* most_roundings) {
                 if (nunits <= kOneStrip) strips = 1;
                 if (most_roundings && strips > 0 && roundings(ntw, WK, steps, (nunits + strips - 1) / strips) > *most_roundings)
                     strips = most < nunits ? most : nunits;
-                if (nunits > 0x3fffffffL || strips < 1 || strips * per_strip > (1 << 20)) continue;
-                const long longest = (nunits + strips - 1) / strips;  // units of the longest strip
+                if (strips < 1 || strips * per_strip > (1 << 20)) continue;
+                const long longest = static_cast<unsigned>(nunits + strips - 1) / static_cast<unsigned>(strips);  // units of the longest strip
                 if (most_roundings && roundings(ntw, WK, steps, longest) > *most_roundings) continue;
                 // Cycles of a unit on one SIMD, the products of its two multiplying waves beside what its two staging waves
                 // do; a fit to all tiles on 17 layers (C, K 4 ... 256, 1 ... 51 taps): what is taken is within 9 % of the
