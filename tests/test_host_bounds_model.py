@@ -243,6 +243,18 @@ def test_windows_that_just_fit_are_taken(model):
             assert _run(model, ps, geom, 0, 0, placement) == (0, "")
 
 
+def test_rounded_planes_do_not_cost_a_turn_of_the_chip(model):
+    """Nor are planes rounded up where a CU then holds a workgroup less and the launch is longer for it: these layers keep
+    the tiles whose planes leave LDS for two workgroups only as they are, where a smaller one took their place."""
+    for ps, geom, tile in [(0, (19, 172, 172, 1624, 5, 10, 20), (4, 4)), (1, (19, 172, 172, 1624, 5, 10, 20), (4, 4)),
+                           (0, (42, 29, 29, 3840, 7, 7, 21), (2, 5)), (0, (8, 64, 144, 39864, 9, 1, 4), (3, 5)),
+                           (1, (21, 4, 44, 46819, 21, 13, 130), (1, 8)), (0, (2, 63, 63, 21736, 9, 1, 1), (1, 6))]:
+        assert _split_tile(model, ps, geom)[:2] == tile, (ps, geom)
+    # planes as they are and rounded up for fewer workgroups per CU
+    for geom in [(3, 33, 20, 1624, 5, 10, 20), (43, 28, 28, 600, 17, 2, 0)]:
+        _check(model, geom, 0, passes=(0, 1), placements=(0, 1))
+
+
 def test_weights_of_the_three_part_kernels_stay_within_32_bits(model):
     """Weights are read at 32-bit byte offsets: a layer of 2^30 weights and more is left to the other kernels."""
     for C, K, S, taken in [(8192, 8192, 15, True), (8192, 8192, 16, False), (4096, 8191, 32, True), (4096, 8192, 32, False)]:
