@@ -191,6 +191,14 @@ __global__ __launch_bounds__(2 * kRole, 4) void split_wgrad_f32_kernel(SwfArgs a
     };
     if (block_wave >= 8) {
         request(u_begin, sets[0]);
+        if (u_end - u_begin == 1) {
+            // no loads of units that are not there (C = K = 4, W = 3992, S = 1 7.3 us with them, now 6.7; N = 21, C = K = 4, W = 584,
+            // S = 49, d = 8 11.2 and 10.0)
+            park(u_begin, lds, sets[0]);
+            __syncthreads();
+            __syncthreads();
+            return;
+        }
         request(min(u_begin + 1, u_end - 1), sets[1]);
         park(u_begin, lds, sets[0]);
         request(min(u_begin + 2, u_end - 1), sets[0]);
@@ -319,8 +327,8 @@ struct Plan {
 // positions of a plane of 8 channels, rounded up so that the two planes of a read begin in different halves of the banks
 long padded(long lx) { return ((lx + 7) & ~15L) + 8; }
 
-// N = 2, C = K = 4, W = 256, S = 5, d = 2, two units: 10.1 us in two strips, 9.3 in one; three units (N = 3,
-// C = K = 16, W = 256, S = 9): 10.0 in three strips, 10.8 in one.
+// N = 2, C = K = 4, W = 256, S = 5, d = 2, two units: 9.0 us in two strips, 8.8 in one (C = K = 32, W = 500, S = 17, d = 4 9.4
+// and 8.9); three units (N = 3, C = K = 16, W = 256, S = 9, d = 2): 9.3 in three strips, 10.5 in one.
 constexpr long kOneStrip = 2;
 
 // taps of a wave, within the 128 registers of 16 waves
