@@ -234,35 +234,37 @@ struct Plan {
 // 256 take 49 on 2000 columns of C = K = 64, S = 33, d = 4 (FP32 instruction 61 us).
 struct Fit {
     bool ok;
-    int nsteps, nstages, planes, resident;
-    int fewer;           // resident workgroups with planes rounded up, where that costs some (0: not one fits)
-    long columns, wlen;  // columns of a window, and slots of a plane of it
-    long per_sample;     // workgroups of a sample
+    int nsteps, nstages, planes, by_regs;
+    long columns, wlen, most_slots;  // columns of a window, slots of a plane of it, and how many 32-bit columns allow
+    long per_sample;                 // workgroups of a sample
     size_t lds;
     double alone, busy;
+    int resident(size_t bytes) const {
+        const int by_lds = bytes > kLdsAll ? 0 : static_cast<int>(static_cast<unsigned>(kLdsAll) / static_cast<unsigned>(bytes));
+        return by_lds < by_regs ? by_lds : by_regs;
+    }
     double time(long grid, int resident) const {
         const long slots = 256L * resident, full = (grid - 1) / slots, last = (grid - full * slots + 255) / 256;
         const double whole = alone > resident * busy ? alone : resident * busy;
         return full * whole + (alone > last * busy ? alone : last * busy);
     }
-    // planes that begin in the same bank (C = K = 48, S = 17, d = 3: 40.0 -> 38.8 us)
-    void round() {
-        const long rounded = (columns + 15) & ~15L;
-        lds += static_cast<size_t>(rounded - wlen) * 48 * planes;
-        wlen = rounded;
-    }
-    // The time of a launch, its planes rounded up where that costs no time: where a CU has room for fewer workgroups so, if
-    // these suffice.  N = 43, C = K = 112, W = 600, S = 17, d = 2 (three for four) 91 and 85 us, but C = 15, K = 5, N = 48,
-    // W = 24848, S = 5, d = 8 (five turns of three for four of four) 29.5 and 31.9, and N = 19, C = K = 172, W = 1624, S = 5,
-    // d = 10 (one for two, or a smaller tile) 88 and 110.
+    // The time of a launch, with planes rounded up to begin in the same bank (C = K = 48, S = 17, d = 3: 40.0 -> 38.8 us) where
+    // that costs no time: where a CU has room for fewer workgroups so, if these suffice.  N = 43, C = K = 112, W = 600, S = 17,
+    // d = 2 (three for four) 91 and 85 us, but C = 15, K = 5, N = 48, W = 24848, S = 5, d = 8 (five turns of three for four of
+    // four) 29.5 and 31.9, and N = 19, C = K = 172, W = 1624, S = 5, d = 10 (one for two, or a smaller tile) 88 and 110.
     double settle(long grid) {
-        const double bare = time(grid, resident);
-        if (fewer < 1 || fewer == resident) return bare;
-        const double t = time(grid, fewer);
-        if (t > bare || (t == bare && grid > 256L * fewer)) return bare;
-        round();
-        resident = fewer;
-        return t;
+        const int bare = resident(lds);
+        const double t = time(grid, bare);
+        const long rounded = (columns + 15) & ~15L;
+        if (planes == 1 || rounded == columns || rounded > most_slots) return t;
+        const size_t bytes = lds + static_cast<size_t>(rounded - columns) * 48 * planes;
+        const int now = resident(bytes);
+        if (now < 1) return t;
+        const double r = now < bare ? time(grid, now) : t;
+        if (r > t || (r == t && now < bare && grid > 256L * now)) return t;
+        wlen = rounded;
+        lds = bytes;
+        return r;
     }
 };
 Fit fit(const CorrProblem& p, Tile t, int sh) {
@@ -270,26 +272,14 @@ Fit fit(const CorrProblem& p, Tile t, int sh) {
     const int tp = 4 >> sh;
     f.nsteps = cdiv(p.S, tp);
     f.nstages = cdiv(p.R, 8 << sh);
-    f.columns = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
-    const int by_regs = 512 / (94 + 12 * t.fbw + 4 * t.fbw * t.pb);
-    auto lds = [&](long wlen) { return (static_cast<size_t>(wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16; };
-    auto resident = [&](size_t bytes) {
-        const int by_lds = bytes > kLdsAll ? 0 : static_cast<int>(static_cast<unsigned>(kLdsAll) / static_cast<unsigned>(bytes));
-        return by_lds < by_regs ? by_lds : by_regs;
-    };
-    f.wlen = f.columns;
-    f.lds = lds(f.wlen);
-    f.resident = resident(f.lds);
-    f.planes = 1 << sh;
+    f.columns = f.wlen = 64L * t.pb + (static_cast<long>(f.nsteps) * tp - 1) * p.d;
+    f.lds = (static_cast<size_t>(f.wlen) * 3 * (1 << sh) + 2 * t.fbw * 192) * 16;
     if (f.wlen > 16384 || f.lds > kLdsAll) return f;
     const long columns = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * 64 * t.pb;  // the last tile may end behind the row
-    const long start = columns - 64 * t.pb - p.P;                                 // of the last window
-    if (columns > 1L << 31 || start + f.wlen > 1L << 31) return f;                // 32-bit columns in the kernel
-    const long rounded = (f.columns + 15) & ~15L;
-    if (sh > 0 && rounded != f.columns && start + rounded <= 1L << 31) {
-        f.fewer = resident(lds(rounded));
-        if (f.fewer == f.resident) f.round();
-    }
+    f.most_slots = (1L << 31) - (columns - 64 * t.pb - p.P);
+    if (columns > 1L << 31 || f.wlen > f.most_slots) return f;  // 32-bit columns in the kernel
+    f.planes = 1 << sh;
+    f.by_regs = 512 / (94 + 12 * t.fbw + 4 * t.fbw * t.pb);
     f.per_sample = static_cast<long>(cdiv(p.Wout, 64 * t.pb)) * cdiv(cdiv(p.M, 16), t.fbw);
     const double window = static_cast<double>(f.columns << sh);
     const double mm = 150.0 * t.fbw * t.pb, loads = 610.0 * t.fbw + 31.0 * (t.fbw + t.pb);
@@ -324,9 +314,8 @@ int planes_shift(const CorrProblem& p) {
         for (int sh = 0; sh <= 2; ++sh) {
             const Fit f = fit(p, t, sh);
             if (!f.ok) continue;
-            const size_t bare = f.lds - static_cast<size_t>(f.wlen - f.columns) * 48 * (1 << sh);
             const double beside = f.nsteps * 600.0 + 1000.0 + (f.columns << sh) * 2.0;
-            const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * bare <= kLdsAll ? 0.5 : 1.0) * beside);
+            const double cost = f.per_sample * f.nstages * (f.nsteps * 96.0 * t.fbw * t.pb + (2 * f.lds <= kLdsAll ? 0.5 : 1.0) * beside);
             if (best >= 0 && cost >= best_cost) continue;
             best_cost = cost;
             best = sh;
