@@ -73,8 +73,8 @@ constexpr size_t kLdsAll = 160 * 1024;
 // Time, forward with S = 51, d = 8 on FP32 instruction and three parts, at 1000, 60000 and 960000 columns: C = K = 15 22.9
 // and 16.2, 24.0 and 22.1, 226 and 130 us; C = K = 12 18.9 and 16.1, 20.0 and 21.9, 177 and 123; C = K = 4 10.6 and 9.0,
 // 10.9 and 12.1, 83 and 63 (four channels are multiplied as eight, twelve as sixteen: slower where one wave of workgroups
-// just fills the chip, faster on either side).  Weight gradient, C = K = 15: 24.3 and 10.1, 31.7 and 20.4, 246 and
-// 123 us.
+// just fills the chip, faster on either side).  Weight gradient, C = K = 15: 24.3 and 9.5, 31.7 and 21.1, 246 and
+// 125 us.
 constexpr long kMinTerms = 16;
 
 // The six products of a step start from zero, smallest first, and their sum is added to the running one in an ordinary

@@ -11,12 +11,13 @@
 // of one strip (few positions, or 129 block pairs and more) has neither.
 //
 // With many taps the matrix instructions bound it, at the clock they are granted with values as dense as these (C = K = 64,
-// S = 33: 1.25 of the 1.33 PFLOP/s that a large product of matrices reaches on such values); with few the loads and the
-// splitting do (S = 5: 62 us, about 55 without the products).  While every wave did both, one filter or two blocks at a time,
-// loads one wave's share of a unit ahead and in lanes that fell on 16 rows (64 cache accesses a load instead of 4) it took, in
-// us, then and now, both stages: N = 8, C = K = 64, W = 20000: S = 5, d = 1 95 and 63, S = 33, d = 4 227 and 212, S = 51, d = 8
-// 341 and 304; N = 16, C = K = 15, W = 60000, S = 51, d = 8 148 and 123; N = 12, C = 24, K = 40, W = 4999, S = 7, d = 3 44 and
-// 21; N = 20, C = K = 48, W = 3001, S = 17, d = 3 64 and 35; N = 8, C = K = 256, W = 2000, S = 3 153 and 90.
+// S = 33: 1.2 PFLOP/s in the first stage, a large product of matrices 1.33 on such values); with few the loads and the splitting
+// do (S = 5: 62 us, about 55 without the products).  While every wave did both, one filter or two blocks at a time, loads one
+// wave's share of a unit ahead and in lanes that fell on 16 rows (64 cache accesses a load instead of 4) it took, in us, then
+// and now, both stages (normal values; events around launches back to back, both builds in turn on one card; a trace of four
+// launches reads up to 15 % more of either): N = 8, C = K = 64, W = 20000: S = 5, d = 1 96 and 63, S = 33, d = 4 234 and 217,
+// S = 51, d = 8 350 and 313; N = 16, C = K = 15, W = 60000, S = 51, d = 8 150 and 125; N = 12, C = 24, K = 40, W = 4999, S = 7, d = 3
+// 44 and 21; N = 20, C = K = 48, W = 3001, S = 17, d = 3 64 and 36; N = 8, C = K = 256, W = 2000, S = 3 155 and 86.
 #include "conv1d_split_f32.h"
 
 namespace conv1d {
